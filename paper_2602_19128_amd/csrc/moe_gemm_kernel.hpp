@@ -90,6 +90,22 @@ __device__ __forceinline__ void copy4_to_lds(const void *g, uint32_t lds_base)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(g) : "memory", "m0");
 }
+// The same with a wavefront-uniform base and a 32-bit offset per lane.
+template <bool NT>
+__device__ __forceinline__ void copy16_to_lds_at(const void *base, uint32_t off, uint32_t lds_base)
+{
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds_base), "v"(off), "s"(base) : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(off), "s"(base) : "memory", "m0");
+}
+// The same as copy16_to_lds<false> where the wavefront-uniform `off` is 0, nothing elsewhere.  The branch is inside the
+// statement: a loop body that stays one basic block keeps the order it is written in.
+__device__ __forceinline__ void copy16_to_lds_if(uint32_t off, const void *g, uint32_t lds_base)
+{
+    asm volatile("s_cmp_lg_u32 %2, 0\n\ts_cbranch_scc1 .Lskip%=\n\ts_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, off\n.Lskip%=:" ::"s"(lds_base), "v"(g), "s"(off) : "memory", "m0", "scc");
+}
 #pragma clang diagnostic pop
 
 // s_waitcnt vmcnt(n) for a wavefront-uniform run-time n (the instruction takes an immediate).
@@ -136,7 +152,13 @@ struct Shape {
     static constexpr int W_RING_BYTES = DW * NW * W_STAGE;
     // one fp32 activation scale per token row, copied 64 rows (one wavefront) at a time
     static constexpr int SC_STAGE_BYTES = FP8 ? ((MB_MAX * 16 + 63) / 64) * 256 : 0;
-    static constexpr int LDS_BYTES = A_RING_BYTES + W_RING_BYTES + (DA + 1) * SC_STAGE_BYTES;
+    static constexpr int RING_BYTES = A_RING_BYTES + W_RING_BYTES + (DA + 1) * SC_STAGE_BYTES;
+    // tiles of TALL_MIN row blocks and more take gemm_tile_tall8 (moe_gemm_tall.hpp): its wavefronts want four
+    // row blocks each
+    static constexpr bool TALL = FP8 && MB_MAX >= 16 && NW == 8 && BPW == 2;
+    static constexpr int TALL_MIN = 8;
+    static constexpr int TALL_BYTES = TALL ? 2 * 256 * 128 + 2 * 256 * 128 + 3 * 256 * 16 : 0;
+    static constexpr int LDS_BYTES = RING_BYTES > TALL_BYTES ? RING_BYTES : TALL_BYTES;
     static_assert(DW >= DA && DA >= 1, "weights are copied at least as far ahead as token rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
     // half-width items (see gemm_tile): wide workgroups only; the fp8 gate/up epilogue needs whole 128-column blocks
@@ -603,6 +625,12 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs &g, const Item item, co
     }   // not SPLITK
 }
 
+}  // namespace
+}  // namespace moe
+#include "moe_gemm_tall.hpp"
+namespace moe {
+namespace {
+
 template <class SH, int NB>
 __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const Item item, const Item next,
                                                 const bool has_next, const bool prefetched, unsigned char *smem)
@@ -612,6 +640,14 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
     } else {
         constexpr int NEXT = NB + 1;
         if (nb <= NB) {
+            if constexpr (SH::TALL && NB >= SH::TALL_MIN) {
+                // (K in whole blocks of four steps, see there; down-projection items of half width stay here)
+                if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0) {
+                    if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
+                    else gemm_tile_tall8<SH, NB, false>(g, item, smem);
+                    return false;
+                }
+            }
             if constexpr (SH::HALF_ITEMS) {
                 if (item.half) return gemm_tile<SH, NB, true>(g, item, next, has_next, prefetched, smem);
                 return gemm_tile<SH, NB, false>(g, item, next, has_next, prefetched, smem);
