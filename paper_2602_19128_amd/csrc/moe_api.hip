@@ -44,18 +44,6 @@ int validate(const moe_config *c)
     return MOE_OK;
 }
 
-// Tile height: the smallest of 16..256 that holds an expert's rows with a binomial safety
-// margin (mean + 4 sigma of a balanced router), so that almost every expert is one tile and its
-// weights are streamed exactly once.
-int tile_rows_for(const moe_config &c)
-{
-    const double mean = (double)c.T * c.top_k / c.E;
-    const double want = mean + 4.0 * sqrt(mean);
-    int rows = 16;
-    while (rows < 256 && rows < want) rows *= 2;
-    return rows;
-}
-
 int max_tiles_for(const moe_config &c)
 {
     const int P = c.T * c.top_k;
@@ -275,7 +263,7 @@ int moe_forward_marked(const moe_config *cfg, const void *x, const float *x_scal
     };
 
     if ((rc = mark()) != MOE_OK) return rc;
-    if (single_launch_mode(*cfg, tr) == MOE_SINGLE_LAUNCH_ALL) {
+    if (single_launch_mode(*cfg) == MOE_SINGLE_LAUNCH_ALL) {
         rc = launch_fused(*cfg, tr, mt, x, router_w, bias, ws + l.route, ids, w, offsets, sorted_pair, inv, tiles,
                           sched, w1, w2, act, y, out, s);
         if (rc != MOE_ERR_UNSUPPORTED) {                      // (a device too small for it takes the pipeline)
@@ -322,7 +310,7 @@ int moe_single_launch_mode(const moe_config *cfg)
 {
     const int rc = validate(cfg);
     if (rc != MOE_OK) return rc;
-    return single_launch_mode(*cfg, tile_rows_for(*cfg));
+    return single_launch_mode(*cfg);
 }
 
 int moe_single_launch_timeouts(uint32_t *count_out)

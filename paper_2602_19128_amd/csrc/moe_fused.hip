@@ -44,8 +44,7 @@ constexpr int FZ_THREADS = 256;
 constexpr int FZ_WAVES = FZ_THREADS / kWave;
 constexpr int FZ_BARRIERS = 4;
 constexpr unsigned long long FZ_WAIT_TICKS = 200000000ull;    // bounded wait: ~2 s of the 100 MHz wall clock
-constexpr int FZ_MAX_PAIRS = 1024;                            // every workgroup sorts all pairs itself
-constexpr int FZ_MAX_EXPERTS = FZ_THREADS;                    // the sort-scatter gives one thread to every local expert
+static_assert(FZ_MAX_EXPERTS <= FZ_THREADS, "the sort-scatter gives one thread to every local expert");
 
 // Barrier counters, each on a cache line of its own.
 struct alignas(128) SyncWord { unsigned v; unsigned pad[31]; };
@@ -187,7 +186,7 @@ __global__ __launch_bounds__(FZ_THREADS) void fused_forward_kernel(FusedArgs a)
         const int per_split = a.rg.tiles_t * a.rg.tiles_e;
         for (int i = block; i < per_split * a.rg.splits; i += nblocks) {
             const int split = i / per_split, r = i % per_split;
-            router_logits_tile<false>(a.x, nullptr, a.router_w, a.zpart, a.tp.T, a.H, a.tp.E, a.rg.k_per_split,
+            router_logits_tile(a.x, a.router_w, a.zpart, a.tp.T, a.H, a.tp.E, a.rg.k_per_split,
                                       r % a.rg.tiles_t, r / a.rg.tiles_t, split, lds);
         }
         sync.meet(bar, bar == 0), ++bar;                      // the partial logits of every H slice are there
@@ -281,19 +280,10 @@ int single_launch_timeouts(unsigned *out)
     return MOE_OK;
 }
 
-// Whether moe_forward runs this problem as one launch (a property of the problem statement and of
-// the switch above; see include/moe.h).
-int single_launch_mode(const moe_config &c, int tile_rows)
+// Whether moe_forward runs this problem as one launch: single_launch_shape and the switch above.
+int single_launch_mode(const moe_config &c)
 {
-    if (!g_enabled.load(std::memory_order_relaxed)) return MOE_SINGLE_LAUNCH_NONE;
-    const long P = (long)c.T * c.top_k;
-    if (c.T <= 0 || P > FZ_MAX_PAIRS || local_experts(c) > FZ_MAX_EXPERTS || c.E > 256) return MOE_SINGLE_LAUNCH_NONE;
-    if (c.dtype != MOE_DTYPE_BF16 || c.quantize_x) return MOE_SINGLE_LAUNCH_NONE;
-    if (!route_few(c) && c.T >= 512) return MOE_SINGLE_LAUNCH_NONE;          // (the matrix-core router's territory)
-    const int mb = tile_rows / 16, est = expected_tiles(c);
-    const bool small = tile_rows <= 64 && gemm_width(mb, true, false, c.I, est) == GEMM_NARROW &&
-                       gemm_width(mb, false, false, c.H, est) == GEMM_NARROW;
-    return small ? MOE_SINGLE_LAUNCH_ALL : MOE_SINGLE_LAUNCH_NONE;
+    return g_enabled.load(std::memory_order_relaxed) && single_launch_shape(c) ? MOE_SINGLE_LAUNCH_ALL : MOE_SINGLE_LAUNCH_NONE;
 }
 
 int launch_fused(const moe_config &c, int tile_rows, int max_tiles, const void *x, const float *router_w,

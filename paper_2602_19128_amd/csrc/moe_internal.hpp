@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <math.h>
+
 #include <atomic>
 
 #include "moe.h"
@@ -98,7 +100,7 @@ int launch_combine(const moe_config &c, const void *y, const float *w, const int
 
 // ---- single-launch forward (moe_fused.hip) -----------------------------------------------------
 void set_single_launch(int enable);
-int single_launch_mode(const moe_config &c, int tile_rows);
+int single_launch_mode(const moe_config &c);
 int single_launch_timeouts(unsigned *out);
 int launch_fused(const moe_config &c, int tile_rows, int max_tiles, const void *x, const float *router_w,
                  const float *bias, void *route_ws, int32_t *ids, float *w, int32_t *offsets, int32_t *sorted_pair,
@@ -151,6 +153,35 @@ inline int expected_tiles(const moe_config &c)
     const long pairs = (long)c.T * c.top_k;
     const int el = local_experts(c);
     return (int)(pairs < el ? pairs : el);
+}
+
+// Tile height: the smallest of 16..256 that holds an expert's rows with a binomial safety
+// margin (mean + 4 sigma of a balanced router), so that almost every expert is one tile and its
+// weights are streamed exactly once.
+inline int tile_rows_for(const moe_config &c)
+{
+    const double mean = (double)c.T * c.top_k / c.E;
+    const double want = mean + 4.0 * sqrt(mean);
+    int rows = 16;
+    while (rows < 256 && rows < want) rows *= 2;
+    return rows;
+}
+
+// Problems that moe_forward runs as one launch once that is switched on (a property of the problem
+// statement; see include/moe.h).
+constexpr int FZ_MAX_PAIRS = 1024;                            // every workgroup sorts all pairs itself
+constexpr int FZ_MAX_EXPERTS = 256;                           // the sort-scatter gives one thread to every local expert
+constexpr int FZ_MAX_TOKENS = 512;                            // tiled FMA logits: beyond this they cost more than the launches saved
+constexpr int RT_FEW = 16;                                    // at most this many experts: logits and routing of a token in one wavefront
+inline bool single_launch_shape(const moe_config &c)
+{
+    const long P = (long)c.T * c.top_k;
+    if (c.T <= 0 || P > FZ_MAX_PAIRS || local_experts(c) > FZ_MAX_EXPERTS || c.E > 256) return false;
+    if (c.dtype != MOE_DTYPE_BF16 || c.quantize_x) return false;
+    if (c.E > RT_FEW && c.T >= FZ_MAX_TOKENS) return false;
+    const int tile_rows = tile_rows_for(c), mb = tile_rows / 16, est = expected_tiles(c);
+    return tile_rows <= 64 && gemm_width(mb, true, false, c.I, est) == GEMM_NARROW &&
+           gemm_width(mb, false, false, c.H, est) == GEMM_NARROW;
 }
 
 // Down projection of a layer with few experts and tall tiles (Mixtral-shaped prefill): the narrow

@@ -2,11 +2,12 @@
 //
 // Few experts (<= 16): router_few_experts_kernel does everything for a token in one wavefront.
 // Otherwise two kernels:
-//   router_logits_kernel  z = x . router_w^T in fp32, LDS-tiled, split along H so that a
-//                         handful of decode tokens still fills the chip; partial sums go
-//                         to scratch and are added in a fixed order (deterministic).
-//   router_logits_mfma_kernel  the same partial sums on the matrix cores (512 tokens and more):
-//                         three bf16 MFMAs per block carry the fp32 weights exactly.
+//   router_logits_mfma_kernel  z = x . router_w^T on the matrix cores, three bf16 MFMAs per block
+//                         carry the fp32 weights exactly; split along H so that a handful of
+//                         decode tokens still fills the chip; partial sums go to scratch and are
+//                         added in a fixed order (deterministic).
+//   router_logits_kernel  the same partial sums with LDS-tiled fp32 FMAs: the layers that the single
+//                         launch may take, which runs this code too.
 //   router_topk_kernel    one 64-lane wavefront per token: scoring rule, optional
 //                         group limiting, then k rounds of a cross-lane arg-max.
 #include "moe_route_device.hpp"
@@ -14,18 +15,17 @@
 namespace moe {
 namespace {
 
-template <bool FP8>
+// (bf16 layers only: those that the single launch may take, see mfma_grid)
 __global__ __launch_bounds__(256) void router_logits_kernel(const void *__restrict__ x,
-                                                            const float *__restrict__ x_scale,
                                                             const float *__restrict__ router_w,
                                                             float *__restrict__ zpart, int T, int H, int E,
                                                             int k_per_split)
 {
     __shared__ LogitsLds lds;
-    router_logits_tile<FP8>(x, x_scale, router_w, zpart, T, H, E, k_per_split, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+    router_logits_tile(x, router_w, zpart, T, H, E, k_per_split, blockIdx.x, blockIdx.y, blockIdx.z, lds);
 }
 
-// ---- many tokens: logits on the matrix cores ---------------------------------------------------
+// ---- logits on the matrix cores ----------------------------------------------------------------
 //
 // Each fp32 router weight is split into three bf16 planes, w = hi + mid + lo (each the bf16
 // rounding of what the previous ones leave; together they carry the 24-bit mantissa), so that
@@ -36,19 +36,17 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const void *__restri
 // loaded (a dozen VALU operations per pair of weights, hidden behind the MFMAs): the weights are
 // read as fp32, 4 bytes per element instead of the 6 of stored planes, and no separate pass runs.
 //
-// A workgroup of 8 wavefronts owns TB*16 tokens x 256 experts x one slice of H.  Wavefront w owns
+// A workgroup of NWV wavefronts owns TB*16 tokens x NWV*32 experts x one slice of H.  Wavefront w owns
 // expert blocks 2w, 2w+1 (16 experts each) against all token blocks; per 32-wide K step the
 // workgroup stages the token rows in LDS (double buffered) while every wavefront loads the weights
 // of its own experts straight into registers, both several steps ahead.  fp8 inputs: the payload
 // is multiplied as is and each 128-wide block's sum is folded in with the token's block scale.
-// The partial logits leave through LDS as whole 1 KiB rows.
+// The partial logits leave through LDS as whole rows.
 typedef __attribute__((ext_vector_type(8))) __bf16 rt_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float rt_f32x4;
 
-constexpr int RM_BE = 256;                 // experts per workgroup tile
+constexpr int RM_MANY_TOKENS = 512;        // from here on the tall workgroups, see mfma_grid
 constexpr int RM_BK = 32;                  // hidden elements per K step (one MFMA deep)
-constexpr int RM_THREADS = 512;
-constexpr int RM_MIN_TOKENS = 512;         // below this the FMA kernel's finer tiles fill the chip better
 
 typedef __attribute__((ext_vector_type(2))) float rt_f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 rt_bf16x2;
@@ -84,13 +82,17 @@ __device__ inline void split_pair(float a, float b, uint32_t &hi, uint32_t &mid,
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
-template <bool FP8, int TB>
-__global__ __launch_bounds__(RM_THREADS) void router_logits_mfma_kernel(const void *__restrict__ x,
+// LDS of a workgroup: the staged output tile (the two token stages fit inside).
+template <int TB, int NWV> constexpr int rm_lds_bytes() { return TB * 16 * (NWV * 32 * 4 + 16); }
+
+template <bool FP8, int TB, int NWV>
+__global__ __launch_bounds__(NWV * 64) void router_logits_mfma_kernel(const void *__restrict__ x,
                                                                         const float *__restrict__ x_scale,
                                                                         const float *__restrict__ router_w,
                                                                         float *__restrict__ zpart, int T, int H, int E,
                                                                         int k_per_split, int splits)
 {
+    constexpr int RM_THREADS = NWV * 64, RM_BE = NWV * 32; // experts per workgroup: 32 per wavefront
     constexpr int BT = TB * 16;                            // tokens per workgroup
     constexpr int X_BYTES = BT * RM_BK * 2;                // one stage of token rows (bf16)
     constexpr int XV = BT * 4 / RM_THREADS;                // 16-byte pieces of x per thread and stage (2 or 1)
@@ -242,6 +244,7 @@ __global__ __launch_bounds__(RM_THREADS) void router_logits_mfma_kernel(const vo
     // is one token's 256 logits (+16 bytes, which spreads the 16 tokens of a write over all banks).
     // The last K step ended with a barrier, so the token stages are free to be overwritten.
     constexpr int OUT_PITCH = RM_BE * 4 + 16;
+    static_assert(2 * X_BYTES <= rm_lds_bytes<TB, NWV>(), "token stages");
 #pragma unroll
     for (int m = 0; m < TB; ++m)
 #pragma unroll
@@ -249,12 +252,13 @@ __global__ __launch_bounds__(RM_THREADS) void router_logits_mfma_kernel(const vo
             *reinterpret_cast<rt_f32x4 *>(rsm + (m * 16 + l16) * OUT_PITCH + ((wave * 2 + b) * 16 + lq * 4) * 4) = acc[b][m];
     __syncthreads();
     float *dst = zpart + (size_t)zs * T * E;
-    const int e = e0 + lane * 4;
+    constexpr int LPR = RM_BE / 4;                         // lanes per row of the tile
+    const int e = e0 + (tid % LPR) * 4;
     const bool vec = (E & 3) == 0 && e + 3 < E;
-    for (int r = wave; r < BT; r += RM_THREADS / 64) {
+    for (int r = tid / LPR; r < BT; r += RM_THREADS / LPR) {
         const int t = t0 + r;
         if (t >= T) break;
-        const rt_f32x4 v = *reinterpret_cast<const rt_f32x4 *>(rsm + r * OUT_PITCH + lane * 16);
+        const rt_f32x4 v = *reinterpret_cast<const rt_f32x4 *>(rsm + r * OUT_PITCH + (tid % LPR) * 16);
         float *row = dst + (size_t)t * E + e;
         if (vec) {
             *reinterpret_cast<rt_f32x4 *>(row) = v;
@@ -292,22 +296,28 @@ __global__ __launch_bounds__(256) void router_few_experts_kernel(const void *__r
 
 }  // namespace
 
-constexpr int RM_OUT_LDS = 8 * 16 * (RM_BE * 4 + 16);    // LDS of the matrix-core logits kernel: the staged output tile
-                                                          // (the two token stages fit inside)
-
-// Matrix-core path: token tile height (in 16-row blocks) and H split.
-struct MfmaGrid { bool use; int tb, tiles_t, tiles_e, splits, k_per_split; };
+// Matrix-core path: workgroup shape and H split.
+//   many tokens   128 tokens x 256 experts by eight wavefronts (256 tokens measured 9 % slower: twice the
+//                 partial logits), one workgroup per compute unit
+//   few tokens    64 tokens x 128 experts by four wavefronts, as many slices of H as the top-k kernel loads
+//                 together: such a call is a chain of memory round trips, and more workgroups with shorter slices
+//                 shorten it.  Against the FMA tiles it replaced, whose stages each waited for their own loads:
+//                 64 DeepSeek tokens 17 -> 8 us, 200 tokens 21 -> 10, 333 tokens of 60 experts 6.9 -> 5.0; logits
+//                 as close to float64 as before.  The line: 1024 fp8 tokens 27 us with tall workgroups, 35 with these,
+//                 1500 bf16 tokens 27 and 47
+struct MfmaGrid { bool use, few; int tiles_t, tiles_e, splits, k_per_split; };
 
 MfmaGrid mfma_grid(const moe_config &c)
 {
     MfmaGrid g{};
-    g.use = c.T >= RM_MIN_TOKENS && c.E > RT_FEW && c.H % RM_BK == 0;
+    // (layers that the single launch may take keep the tiled FMA logits, which both run)
+    g.use = c.E > RT_FEW && !single_launch_shape(c);
     if (!g.use) return g;
-    g.tb = 8;                                              // 128 tokens per workgroup (256 measured 9 % slower: twice the partial logits)
-    g.tiles_t = ceil_div(c.T, g.tb * 16);
-    g.tiles_e = ceil_div(c.E, RM_BE);
+    g.few = c.T < RM_MANY_TOKENS;
+    g.tiles_t = ceil_div(c.T, g.few ? 64 : 128);
+    g.tiles_e = ceil_div(c.E, g.few ? 128 : 256);
     const int chunks = c.H / RM_BK;
-    int want = ceil_div(256, g.tiles_t * g.tiles_e);       // one workgroup per compute unit
+    int want = ceil_div(256, g.tiles_t * g.tiles_e);
     if (want > RT_MAX_SPLIT) want = RT_MAX_SPLIT;
     if (want > chunks) want = chunks;
     if (want < 1) want = 1;
@@ -316,6 +326,19 @@ MfmaGrid mfma_grid(const moe_config &c)
     g.k_per_split = per;
     g.splits = ceil_div(c.H, per);
     return g;
+}
+
+template <bool FP8, int TB, int NWV>
+int launch_logits_mfma(const MfmaGrid &m, const moe_config &c, const void *x, const float *x_scale,
+                       const float *router_w, float *zpart, hipStream_t s)
+{
+    auto kern = router_logits_mfma_kernel<FP8, TB, NWV>;
+    static DeviceOnce lds_limit_set;
+    const int rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), rm_lds_bytes<TB, NWV>());
+    if (rc != MOE_OK) return rc;
+    hipLaunchKernelGGL(kern, dim3(m.tiles_t * m.splits, m.tiles_e, 1), dim3(NWV * 64), (rm_lds_bytes<TB, NWV>()), s, x, x_scale,
+                       router_w, zpart, c.T, c.H, c.E, m.k_per_split, m.splits);
+    return check_launch();
 }
 
 size_t route_workspace_bytes(const moe_config &c)
@@ -357,33 +380,17 @@ int launch_route(const moe_config &c, const void *x, const float *x_scale, const
     float *zpart = static_cast<float *>(ws);
     const MfmaGrid m = mfma_grid(c);
     if (m.use) {
-        int rc;
-        const dim3 grid(m.tiles_t * m.splits, m.tiles_e, 1);
-        if (c.dtype == MOE_DTYPE_FP8_E4M3) {
-            auto kern = router_logits_mfma_kernel<true, 8>;
-            static DeviceOnce lds_limit_set;
-            if ((rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), RM_OUT_LDS)) != MOE_OK) return rc;
-            hipLaunchKernelGGL(kern, grid, dim3(RM_THREADS), RM_OUT_LDS, s, x, x_scale, router_w, zpart, c.T, c.H, c.E,
-                               m.k_per_split, m.splits);
-        } else {
-            auto kern = router_logits_mfma_kernel<false, 8>;
-            static DeviceOnce lds_limit_set;
-            if ((rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), RM_OUT_LDS)) != MOE_OK) return rc;
-            hipLaunchKernelGGL(kern, grid, dim3(RM_THREADS), RM_OUT_LDS, s, x, x_scale, router_w, zpart, c.T, c.H, c.E,
-                               m.k_per_split, m.splits);
-        }
-        rc = check_launch();
+        const bool f8 = c.dtype == MOE_DTYPE_FP8_E4M3;
+        const int rc = m.few ? (f8 ? launch_logits_mfma<true, 4, 4>(m, c, x, x_scale, router_w, zpart, s)
+                                   : launch_logits_mfma<false, 4, 4>(m, c, x, x_scale, router_w, zpart, s))
+                             : (f8 ? launch_logits_mfma<true, 8, 8>(m, c, x, x_scale, router_w, zpart, s)
+                                   : launch_logits_mfma<false, 8, 8>(m, c, x, x_scale, router_w, zpart, s));
         if (rc != MOE_OK) return rc;
         p.splits = m.splits;
     } else {
         const RouteGrid g = route_grid(c);
         const dim3 grid(g.tiles_t, g.tiles_e, g.splits);
-        if (c.dtype == MOE_DTYPE_FP8_E4M3)
-            hipLaunchKernelGGL(router_logits_kernel<true>, grid, dim3(256), 0, s, x, x_scale, router_w, zpart,
-                               c.T, c.H, c.E, g.k_per_split);
-        else
-            hipLaunchKernelGGL(router_logits_kernel<false>, grid, dim3(256), 0, s, x, x_scale, router_w, zpart,
-                               c.T, c.H, c.E, g.k_per_split);
+        hipLaunchKernelGGL(router_logits_kernel, grid, dim3(256), 0, s, x, router_w, zpart, c.T, c.H, c.E, g.k_per_split);
         int rc = check_launch();
         if (rc != MOE_OK) return rc;
         p.splits = g.splits;

@@ -64,9 +64,7 @@ __device__ inline void load_x8(const void *x, const float *x_scale, int T, int H
 // threads: z = x . router_w^T in fp32, LDS-tiled.  As / Bs are the workgroup's two LDS stages.
 struct LogitsLds { float As[RT_BK][RT_TM + RT_PAD]; float Bs[RT_BK][RT_TN + RT_PAD]; };
 
-template <bool FP8>
-__device__ __forceinline__ void router_logits_tile(const void *__restrict__ x, const float *__restrict__ x_scale,
-                                                   const float *__restrict__ router_w, float *__restrict__ zpart,
+__device__ __forceinline__ void router_logits_tile(const void *__restrict__ x, const float *__restrict__ router_w, float *__restrict__ zpart,
                                                    int T, int H, int E, int k_per_split, int tile_t, int tile_e,
                                                    int split, LogitsLds &lds)
 {
@@ -87,7 +85,7 @@ __device__ __forceinline__ void router_logits_tile(const void *__restrict__ x, c
 
     for (int k0 = kbeg; k0 < kend; k0 += RT_BK) {
         float xv[8], wv[8];
-        load_x8<FP8>(x, x_scale, T, H, t0 + lrow, k0 + lk, xv);
+        load_x8<false>(x, nullptr, T, H, t0 + lrow, k0 + lk, xv);
         if (e0 + lrow < E && k0 + lk < H) {
             const float4 *src = reinterpret_cast<const float4 *>(router_w + (size_t)(e0 + lrow) * H + k0 + lk);
             const float4 a = src[0], b = src[1];
@@ -378,7 +376,6 @@ __device__ __forceinline__ void router_topk_token(const float *__restrict__ zpar
 // Few experts (E <= RT_FEW): logits and routing of a token in one wavefront, one launch.  The
 // lanes split H (8 consecutive elements per lane and pass); every lane keeps one running sum per
 // expert, a butterfly adds them across the wavefront in a fixed order.
-constexpr int RT_FEW = 16;
 
 // WPT wavefronts share a token (each takes a contiguous part of H, the parts are added in wavefront
 // order): with few tokens one wavefront per token leaves most of the chip idle and is bound by the
