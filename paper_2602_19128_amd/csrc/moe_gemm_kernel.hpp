@@ -161,8 +161,9 @@ struct Shape {
     static constexpr int LDS_BYTES = RING_BYTES > TALL_BYTES ? RING_BYTES : TALL_BYTES;
     static_assert(DW >= DA && DA >= 1, "weights are copied at least as far ahead as token rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
-    // half-width items (see gemm_tile): wide workgroups only; the fp8 gate/up epilogue needs whole 128-column blocks
-    static constexpr bool HALF_ITEMS = NW >= 8 && !(FP8 && SWIGLU) && !SPLITK;
+    // half-width items (see gemm_tile): wide workgroups of launches in whole ranges only (gemm_whole_ranges); the
+    // fp8 gate/up epilogue needs whole 128-column blocks
+    static constexpr bool HALF_ITEMS = NW >= 8 && !(FP8 && SWIGLU) && !SPLITK && MB_MAX >= 4;
     static_assert(!(FP8 && SWIGLU) || COLS == kQBlock, "fp8 gate/up: a workgroup re-quantises one 1x128 block per row");
 };
 
@@ -667,6 +668,7 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
 //   whole_ranges = 1: part r is work range r, whole tiles only.  With few tiles per XCD this
 //     keeps each XCD on as few tiles at a time as possible (their token rows compete with the
 //     weight stream for its L2; measured +20 % on a 32-expert share when parts cut through tiles).
+//     Not for low tiles, see gemm_whole_ranges.
 //   whole_ranges = 0: the sequence is cut into eight equal parts, which coincide with the ranges
 //     up to a tile or two at their ends.  Every tile streams the same weight bytes, so with many
 //     tiles per XCD equal item counts are what lets the XCDs finish together.
@@ -781,7 +783,7 @@ int launch_shape(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched,
     // of a last round) keeps the loop in the kernel at one trip
     const int part_slots = (ceil_div(max_tiles, GM_XCDS) + 1) * col_tiles + (SH::HALF_ITEMS ? round_slots / 2 : 0);
     const int blocks = part_slots * GM_XCDS;
-    const int whole_ranges = est_tiles <= 8 * GM_XCDS ? 1 : 0;   // at most eight tiles per XCD
+    const int whole_ranges = gemm_whole_ranges(SH::MB_MAX, g.K * (SH::FP8 ? 1 : 2) / GM_STEP_BYTES, est_tiles) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(SH::THREADS), SH::LDS_BYTES, s, g, tiles, sched, col_tiles, whole_ranges,
                        round_slots);
     return check_launch();
@@ -794,6 +796,10 @@ struct ShapesFor {
     static constexpr int DW = 2;
     using Wide = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8>;
     using Narrow = Shape<MB_MAX, 4, DA, 3, SWIGLU, FP8>;
+    // Low tiles with a long K: the copies of a step are waited for in the order they were issued, so what is in
+    // flight is DA + 1 stages whatever DW says, and a launch of fewer workgroups than compute units (three Mixtral
+    // tokens: 192) streamed at 5.7 TB/s with 32 KiB each; with 64 KiB 6.6 (down projection 124 -> 107 us).
+    using NarrowDeep = Shape<MB_MAX, 4, MB_MAX <= 2 ? 4 : DA, MB_MAX <= 2 ? 5 : 3, SWIGLU, FP8>;
     using Wide4 = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8, SWIGLU ? 2 : 4>;
     using WideSplit = Shape<MB_MAX, 8, DA, DW, false, false, 2, true>;
 };
@@ -814,6 +820,9 @@ int launch_for_rows(const GemmArgs &g, const moe_tile *tiles, const int32_t *sch
             return launch_shape<typename SF::Wide4>(g, tiles, sched, max_tiles, est_tiles, s);
         return MOE_ERR_UNSUPPORTED;
     case GEMM_NARROW:
+        if constexpr (!(FP8 && SWIGLU) && MB_MAX <= 2)
+            if (g.K * (FP8 ? 1 : 2) / GM_STEP_BYTES >= kLongK)
+                return launch_shape<typename SF::NarrowDeep>(g, tiles, sched, max_tiles, est_tiles, s);
         if constexpr (!(FP8 && SWIGLU))
             return launch_shape<typename SF::Narrow>(g, tiles, sched, max_tiles, est_tiles, s);
         return MOE_ERR_UNSUPPORTED;

@@ -155,6 +155,20 @@ inline int expected_tiles(const moe_config &c)
     return (int)(pairs < el ? pairs : el);
 }
 
+// K steps from which a workgroup's stream, and not its start, is its time: low tiles choose their launch by it
+// (16 tokens of 256 x 128 experts, 4 and 2 steps: 22.1 us a layer with the simple launch, 23.1 with the other).
+constexpr int kLongK = 16;
+
+// Whether XCD r works through work range r, whole tiles only, or through one of eight equal parts of the items
+// (see gemm_items): whole ranges when an XCD has at most eight tiles and they are 64 rows or taller.  Token rows of
+// lower tiles are too few to matter to an L2, while ranges of whole tiles leave XCDs idle: three Mixtral tokens hit
+// six experts, six ranges (gate/up 269 -> 205 us with equal parts); fp8 share of 26 32-row tiles, three or four a
+// range, down 66 -> 59 us.  64-row tiles of 60 experts: gate/up 39 us in whole ranges, 45 in equal parts.
+inline bool gemm_whole_ranges(int mb_max, int k_steps, int est_tiles)
+{
+    return est_tiles <= 8 * MOE_WORK_RANGES && (mb_max >= 4 || k_steps < kLongK);
+}
+
 // Tile height: the smallest of 16..256 that holds an expert's rows with a binomial safety
 // margin (mean + 4 sigma of a balanced router), so that almost every expert is one tile and its
 // weights are streamed exactly once.

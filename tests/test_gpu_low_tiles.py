@@ -1,0 +1,39 @@
+"""Grouped GEMMs of a handful of tokens on few, wide experts: fewer tiles than XCDs in equal parts, the deep copy rings
+of low tiles with fewer K steps than stages and with many, 16- and 32-row tiles, experts without a row."""
+import pytest
+import torch
+
+from paper_2602_19128_amd import binding as moe
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows, H, I", [
+    ([1], 64, 64), ([2, 0, 1, 0, 0, 3], 128, 320), ([1, 1, 0, 1, 1, 1, 1], 1024, 4160), ([16, 15, 1], 576, 2048),
+    ([17, 32, 1, 9], 448, 1024), ([12] * 40, 256, 192),
+])
+def test_low_tiles_of_few_experts(rows, H, I):
+    E, T = len(rows), sum(rows)
+    cfg = moe.MoEConfig(T, H, I, E, 1, 0, 1, 1, 1, 1, 0, 1.0, 0, 0, 0)
+    plan = moe.moe_gemm_plan(cfg, "down")
+    assert plan["tile_rows"] <= 32 and plan["wavefronts"] == 4 and plan["whole_ranges"] == (I < 1024)
+    gen = torch.Generator("cuda").manual_seed(H + I)
+    ids = torch.repeat_interleave(torch.arange(E), torch.tensor(rows)).cuda()[torch.randperm(T, generator=gen, device="cuda")]
+    ids = ids.to(torch.int32).view(T, 1)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    x, w1, w2 = draw(T, H).bfloat16(), (draw(E, 2 * I, H) * H ** -0.5).bfloat16(), (draw(E, H, I) * I ** -0.5).bfloat16()
+    offsets, pair, inv, tiles, sched = moe.moe_permute(cfg, ids)
+    act, _ = moe.moe_grouped_gemm_swiglu(cfg, x, None, w1, None, pair, tiles, sched)
+    y = moe.moe_grouped_gemm_down(cfg, act, None, w2, None, tiles, sched)
+    off = offsets.tolist()
+    for e in range(E):
+        lo, hi = off[e], off[e + 1]
+        xe, w = x[pair[lo:hi].long()].double(), w1[e].double().t()
+        gu = xe @ w
+        ref = torch.nn.functional.silu(gu[:, :I]) * gu[:, I:]
+        # one bf16 rounding (2^-9 of the value) of fp32 sums of up to 4160 terms (2^-24 each, of the sum of magnitudes)
+        slack = (xe.abs() @ w.abs()).max() ** 2 * 2.0 ** -20 if hi > lo else 0.0
+        assert ((act[lo:hi].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all(), f"gate/up, expert {e}"
+        a, w = act[lo:hi].double(), w2[e].double().t()
+        ref = a @ w
+        assert ((y[lo:hi].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + (a.abs() @ w.abs()) * 2.0 ** -20).all(), f"down, expert {e}"
