@@ -147,12 +147,6 @@ __device__ inline uint32_t orderable(float f)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// (key, expert) packed so that an unsigned max picks the larger key, then the lower index.
-__device__ inline unsigned long long pack_key(float c, int e)
-{
-    return ((unsigned long long)orderable(c) << 32) | (unsigned long long)(0xffffffffu - (uint32_t)e);
-}
-
 // Partner exchange of an all-reduce butterfly over the 64 lanes, step by step (STEP = 0..5 joins
 // groups of 2^STEP lanes into groups of twice the size).  Inside a row of 16 lanes the value
 // comes through DPP, which costs no more than the ALU operation it feeds: swaps inside a quad for
@@ -172,25 +166,25 @@ __device__ __forceinline__ uint32_t butterfly_partner(uint32_t v)
     else return (uint32_t)__shfl_xor((int)v, 32, kWave);
 }
 
-template <int STEP>
-__device__ __forceinline__ unsigned long long butterfly_max_u64(unsigned long long v)
+// max over aligned segments of `width` lanes (width = power of two <= 64; the same on every lane)
+__device__ inline uint32_t seg_max_u32(uint32_t v, int width)
 {
-    const uint32_t lo = butterfly_partner<STEP>((uint32_t)v);
-    const uint32_t hi = butterfly_partner<STEP>((uint32_t)(v >> 32));
-    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    return o > v ? o : v;
+    if (width > 1) v = max(v, butterfly_partner<0>(v));
+    if (width > 2) v = max(v, butterfly_partner<1>(v));
+    if (width > 4) v = max(v, butterfly_partner<2>(v));
+    if (width > 8) v = max(v, butterfly_partner<3>(v));
+    if (width > 16) v = max(v, butterfly_partner<4>(v));
+    if (width > 32) v = max(v, butterfly_partner<5>(v));
+    return v;
 }
 
-// max over aligned segments of `width` lanes (width = power of two <= 64; the same on every lane)
-__device__ inline unsigned long long seg_max_u64(unsigned long long v, int width)
+// max over the wavefront, as a scalar: DPP inside the four rows of 16 lanes, scalar registers across them (no LDS)
+__device__ inline uint32_t wave_max_u32(uint32_t v)
 {
-    if (width > 1) v = butterfly_max_u64<0>(v);
-    if (width > 2) v = butterfly_max_u64<1>(v);
-    if (width > 4) v = butterfly_max_u64<2>(v);
-    if (width > 8) v = butterfly_max_u64<3>(v);
-    if (width > 16) v = butterfly_max_u64<4>(v);
-    if (width > 32) v = butterfly_max_u64<5>(v);
-    return v;
+    v = seg_max_u32(v, 16);
+    const uint32_t a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const uint32_t c = __builtin_amdgcn_readlane((int)v, 32), d = __builtin_amdgcn_readlane((int)v, 48);
+    return max(max(a, b), max(c, d));
 }
 
 __device__ inline float wave_max_f32(float v)
@@ -230,7 +224,11 @@ __device__ __forceinline__ void route_token(const float (&z)[EPL], int lane, int
 {
     const int E = p.E;
     float s[EPL];
-    unsigned long long key[EPL];
+    // Keys are 32 bits, larger is better, 0 = not a candidate.  A maximum is found on the keys alone; among equal
+    // ones the lowest expert is the first one of the lowest lane that holds it, which a ballot tells.  (With the index in
+    // the low half of 64-bit keys every step of a reduction was five instructions: top-k of 64 tokens 9.0 -> 7.4 us, of
+    // 4096 tokens 14.3 -> 11.8, of 16384 tokens 31 -> 24.)
+    uint32_t key[EPL];
     if (p.scoring == MOE_SCORE_SOFTMAX) {
         float m = -INFINITY;
 #pragma unroll
@@ -253,7 +251,7 @@ __device__ __forceinline__ void route_token(const float (&z)[EPL], int lane, int
     for (int i = 0; i < EPL; ++i) {
         const int e = lane * EPL + i;
         const float c = s[i] + ((bias != nullptr && e < E) ? bias[e] : 0.f);
-        key[i] = (e < E) ? pack_key(c, e) : 0ull;          // 0 = not a candidate
+        key[i] = (e < E) ? orderable(c) : 0u;
     }
 
     // ---- group limiting ----------------------------------------------------
@@ -261,51 +259,58 @@ __device__ __forceinline__ void route_token(const float (&z)[EPL], int lane, int
         const int gsz = E / p.n_group;
         const int lpg = gsz / EPL;                         // lanes per group (power of two)
         const int my_group = lane / lpg;
-        unsigned long long left[EPL];
+        const int seg = my_group * lpg;                    // first lane of this lane's group
+        uint32_t left[EPL];
 #pragma unroll
         for (int i = 0; i < EPL; ++i) left[i] = key[i];
         float gscore = 0.f;
         for (int n = 0; n < p.group_score_topn; ++n) {
-            unsigned long long best = 0ull;
+            uint32_t mine = left[0];
 #pragma unroll
-            for (int i = 0; i < EPL; ++i) best = left[i] > best ? left[i] : best;
-            best = seg_max_u64(best, lpg);
+            for (int i = 1; i < EPL; ++i) mine = max(mine, left[i]);
+            const uint32_t best = seg_max_u32(mine, lpg);
+            // the first lane of the group that holds it drops its first copy
+            const unsigned long long holders = __ballot(mine == best) >> seg;
+            bool drop = lane - seg == (int)__builtin_ctzll(holders);
 #pragma unroll
-            for (int i = 0; i < EPL; ++i) if (left[i] == best) left[i] = 0ull;
+            for (int i = 0; i < EPL; ++i)
+                if (drop && left[i] == best) { left[i] = 0u; drop = false; }
             // undo the order-preserving map to get the key value back
-            const uint32_t ob = (uint32_t)(best >> 32);
-            const uint32_t fb = (ob & 0x80000000u) ? (ob & 0x7fffffffu) : ~ob;
-            gscore += (best != 0ull) ? __uint_as_float(fb) : 0.f;
+            const uint32_t fb = (best & 0x80000000u) ? (best & 0x7fffffffu) : ~best;
+            gscore += (best != 0u) ? __uint_as_float(fb) : 0.f;
         }
         int rank = 0;
         for (int g = 0; g < p.n_group; ++g) {
-            const float og = __shfl(gscore, g * lpg, kWave);
+            const float og = __uint_as_float(__builtin_amdgcn_readlane(__float_as_int(gscore), g * lpg));
             rank += (og > gscore) || (og == gscore && g < my_group);
         }
         const bool kept = my_group < p.n_group && rank < p.topk_group;
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) if (!kept) key[i] = 0ull;
+        for (int i = 0; i < EPL; ++i) if (!kept) key[i] = 0u;
     }
 
     // ---- k rounds of wave-wide arg-max ----------------------------------------
     int my_id = 0;
-    float my_s = 0.f;
+    float my_s = 0.f, sum = 0.f;                           // (sum: in slot order)
     for (int j = 0; j < p.top_k; ++j) {
-        unsigned long long best = 0ull;
+        uint32_t mine = key[0];
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) best = key[i] > best ? key[i] : best;
-        best = seg_max_u64(best, kWave);
-        int e = (int)(0xffffffffu - (uint32_t)best);
-        e = e < 0 ? 0 : (e >= E ? E - 1 : e);              // keeps ids in range whatever the inputs
-        float sel = 0.f;
+        for (int i = 1; i < EPL; ++i) mine = max(mine, key[i]);
+        const uint32_t best = wave_max_u32(mine);
+        const int src = __builtin_ctzll(__ballot(mine == best));   // (some lane holds it)
+        int at = EPL - 1;                                  // this lane's first copy
+        float sv = s[EPL - 1];
+#pragma unroll
+        for (int i = EPL - 2; i >= 0; --i)
+            if (key[i] == best) { at = i; sv = s[i]; }
+        const int e = min(src * EPL + __builtin_amdgcn_readlane(at, src), E - 1);   // in range whatever the inputs
+        const float sel = __uint_as_float(__builtin_amdgcn_readlane(__float_as_int(sv), src));
 #pragma unroll
         for (int i = 0; i < EPL; ++i)
-            if (lane * EPL + i == e) { sel = s[i]; key[i] = 0ull; }
-        sel = __shfl(sel, e / EPL, kWave);
+            if (lane == src && i == at) key[i] = 0u;
+        sum += sel;
         if (lane == j) { my_id = e; my_s = sel; }
     }
-    float sum = 0.f;
-    for (int j = 0; j < p.top_k; ++j) sum += __shfl(my_s, j, kWave);   // slot order
     if (lane < p.top_k) {
         float wt = my_s;
         if (p.renormalize) wt = wt / sum;
