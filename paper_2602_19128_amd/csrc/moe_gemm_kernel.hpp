@@ -153,11 +153,11 @@ struct Shape {
     // one fp32 activation scale per token row, copied 64 rows (one wavefront) at a time
     static constexpr int SC_STAGE_BYTES = FP8 ? ((MB_MAX * 16 + 63) / 64) * 256 : 0;
     static constexpr int RING_BYTES = A_RING_BYTES + W_RING_BYTES + (DA + 1) * SC_STAGE_BYTES;
-    // tiles of TALL_MIN row blocks and more take gemm_tile_tall8 (moe_gemm_tall.hpp): its wavefronts want four
-    // row blocks each
-    static constexpr bool TALL = FP8 && MB_MAX >= 16 && NW == 8 && BPW == 2;
-    static constexpr int TALL_MIN = 8;
-    static constexpr int TALL_BYTES = TALL ? 2 * 256 * 128 + 2 * 256 * 128 + 3 * 256 * 16 : 0;
+    // Tall tiles (moe_gemm_tall.hpp).  fp8: TALL_MIN row blocks and more take gemm_tile_tall8, whose wavefronts want
+    // four row blocks each.  bf16: nine row blocks and more of an expert with TALL_COUNT tiles take gemm_tile_tall16.
+    static constexpr bool TALL = MB_MAX >= 16 && NW == 8 && BPW == 2;
+    static constexpr int TALL_MIN = FP8 ? 8 : 9, TALL_COUNT = 3;
+    static constexpr int TALL_BYTES = !TALL ? 0 : FP8 ? 4 * 256 * 128 + 3 * 256 * 16 : 5 * 256 * 128;
     static constexpr int LDS_BYTES = RING_BYTES > TALL_BYTES ? RING_BYTES : TALL_BYTES;
     static_assert(DW >= DA && DA >= 1, "weights are copied at least as far ahead as token rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
@@ -642,10 +642,15 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
         constexpr int NEXT = NB + 1;
         if (nb <= NB) {
             if constexpr (SH::TALL && NB >= SH::TALL_MIN) {
-                // (K in whole blocks of four steps, see there; down-projection items of half width stay here)
-                if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0) {
-                    if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
-                    else gemm_tile_tall8<SH, NB, false>(g, item, smem);
+                // (down-projection items of half width stay here)
+                if constexpr (SH::FP8) {
+                    if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0) {   // K in whole blocks of four steps, see there
+                        if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
+                        else gemm_tile_tall8<SH, NB, false>(g, item, smem);
+                        return false;
+                    }
+                } else if (!item.half && item.tile.count >= SH::TALL_COUNT) {
+                    gemm_tile_tall16<SH, (NB + 1) / 2>(g, item, smem);
                     return false;
                 }
             }

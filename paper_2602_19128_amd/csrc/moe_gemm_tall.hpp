@@ -343,5 +343,320 @@ __device__ __forceinline__ void gemm_tile_tall8(const GemmArgs &g, const Item &i
     else tall8_wave<SH, NB, N1, N0, SHARE>(t);
 }
 
+// ---- bf16 ------------------------------------------------------------------------------------------------------
+//
+// Tall tiles of experts with three and more of them (long prompts on few experts: the matrix cores' regime).  The same
+// grid of wavefronts and the same kind of step on v_mfma_f32_32x32x16_bf16: one wavefront alone issues 60 % of the
+// 16x16x32 rate and all of this one, so a matrix pipe keeps busy while its other wavefront waits.  Fragments are
+// requested PF groups of two MFMAs ahead; the barrier of a step sits before its last groups.  Weights have three
+// stages of LDS (their lines come from HBM), token rows two.
+// 4096 Mixtral tokens: gate/up 1708 -> 1658 us, down 866 -> 833 (a library GEMM of the same shape: 1615 for the
+// gate/up part).  The clock is down to 1.65 to 1.8 GHz there: what is left is power more than cycles.
+// For experts of one or two tiles, whose weight stream is the time, gemm_tile is the faster one (4096 DeepSeek tokens,
+// gate/up 2736 us against 2793 with this for all tall tiles): there a wavefront refills its own weights without a barrier.
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// LDS of a tall bf16 tile: two stages of token rows, three of weights.
+template <class SH>
+struct Tall16 {
+    static constexpr int A_STAGE = 256 * 128, W_STAGE = 256 * 128;
+    static constexpr int W_RING = 2 * A_STAGE;
+    static constexpr int LDS_BYTES = W_RING + 3 * W_STAGE;
+    static_assert(LDS_BYTES <= SH::LDS_BYTES, "the launch reserves it");
+};
+
+// What a wavefront of gemm_tile_tall16 knows about its tile.
+struct Tall16Args {
+    const GemmArgs &g;
+    const moe_tile &tile;
+    unsigned char *smem;
+    int tid, lane, wave, ct, kh, nk, koff;
+    size_t row_bytes, kbase;
+};
+
+// One wavefront's part: NBT blocks of 32 token rows (the first is block TB0 of the tile's TB) times 64 weight rows.
+template <class SH, int TB, int NBT, int TB0>
+__device__ __forceinline__ void tall16_wave(const Tall16Args &t)
+{
+    using TL = Tall16<SH>;
+    constexpr bool SWIGLU = SH::SWIGLU;
+    constexpr int NW = SH::NW, WB = 2;                        // 32-row weight blocks per wavefront
+    constexpr int A_PASS = (4 * TB + NW - 1) / NW;            // 8-row token copies per wavefront and step
+    constexpr int W_PASS = 4;                                 // 8-row weight copies per wavefront and step
+    constexpr int NKK = 4;                                    // 16-wide MFMA steps of a K step
+    constexpr int NQ = NKK * NBT;                             // token fragments (groups of WB MFMAs) of a step
+    constexpr int PF = NBT > 1 ? 4 : 2;                       // fragments requested ahead
+    static_assert(NQ % PF == 0, "a fragment keeps its registers from step to step");
+    constexpr int QB = NQ - PF + 1;                           // group after which the next stage is opened
+    static_assert(QB >= (NKK - 2) * NBT, "the last weight fragments are requested before the stage is given up");
+    constexpr int CPG = (A_PASS + W_PASS + QB) / (QB + 1);    // copies issued per group: all of them before that point
+    constexpr int NPRE = (NQ - QB) * CPG < A_PASS ? (NQ - QB) * CPG : A_PASS;   // token copies issued right after it
+
+    const GemmArgs &g = t.g;
+    const moe_tile &tile = t.tile;
+    unsigned char *const smem = t.smem;
+    const int lane = t.lane, wave = t.wave, ct = t.ct, nk = t.nk;
+    const int wn = wave & 3;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int crow = lane >> 3;
+    // LDS row r holds logical 16-byte chunk c at place c ^ (r & 7) ^ (r >> 3 & 1): the sixteen rows that a
+    // 16-byte fragment read serves at a time then cover all banks
+    const int cbyte = ((lane & 7) ^ crow) << 4;
+    const int rows = tile.rows;
+    const int n_out = g.n_out;
+    const int w_rows = SWIGLU ? 2 * n_out : n_out;
+
+    // weight copies: this wavefront moves LDS rows 32*wave .. 32*wave+31 of the stage.  A quarter of the
+    // gate/up slab holds its 32 gate rows, then the matching up rows.
+    const int wcol0 = ct * SH::COLS + (SWIGLU ? (wave >> 1) * 32 : wave * 32);     // first output column of these rows
+    const int wc0 = __builtin_amdgcn_readfirstlane(min(wcol0, n_out - 1));
+    const unsigned char *w_base = g.W + ((size_t)tile.expert * w_rows + (SWIGLU && (wave & 1) ? n_out : 0) + wc0) * t.row_bytes + t.kbase;
+    uint32_t w_off[W_PASS];
+#pragma unroll
+    for (int q = 0; q < W_PASS; ++q)                          // columns past the end repeat the last one; never stored
+        w_off[q] = (uint32_t)(min(wcol0 + q * 8 + crow, n_out - 1) - wc0) * (uint32_t)t.row_bytes + (cbyte ^ (q & 1) * 16);
+    const unsigned char *a_ptr[A_PASS];
+#pragma unroll
+    for (int i = 0; i < A_PASS; ++i) {
+        const int r = min(8 * (wave + NW * i) + crow, rows - 1);   // padded rows repeat the last row; never stored
+        size_t src;
+        if constexpr (SWIGLU) src = (size_t)(g.sorted_pair[tile.row0 + r] / g.top_k);
+        else src = (size_t)(tile.row0 + r);
+        a_ptr[i] = g.A + src * t.row_bytes + t.kbase + (cbyte ^ (wave & 1) * 16);
+    }
+    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(lds_addr_of(smem)) + wave * 1024;
+    const uint32_t w_lds = a_lds + TL::W_RING + wave * ((W_PASS - 1) * 1024);
+
+    f32x16 acc[NBT][WB];
+#pragma unroll
+    for (int m = 0; m < NBT; ++m)
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][b][v] = 0.f;
+
+    // where the next token / weight copies read and write: byte offset along K (wraps around), LDS address
+    const int k_end = nk * GM_STEP_BYTES;
+    int ka = t.koff * GM_STEP_BYTES, kw = ka;
+    uint32_t a_dst = a_lds, w_dst = w_lds;
+    auto advance = [&](int &k) __attribute__((always_inline)) { k += GM_STEP_BYTES; k = k == k_end ? 0 : k; };
+    auto copy_token = [&](int i) __attribute__((always_inline)) {
+        copy16_to_lds<false>(a_ptr[i] + ka, a_dst + i * (NW * 1024));
+        if (i == A_PASS - 1) { advance(ka); a_dst = a_dst == a_lds ? a_lds + TL::A_STAGE : a_lds; }
+    };
+    auto copy_weight = [&](int i) __attribute__((always_inline)) {
+        copy16_to_lds_at<false>(w_base + kw, w_off[i], w_dst + i * 1024);
+        if (i == W_PASS - 1) { advance(kw); w_dst = w_dst == w_lds + 2 * TL::W_STAGE ? w_lds : w_dst + TL::W_STAGE; }
+    };
+    auto copy_tokens = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < A_PASS; ++i) copy_token(i);
+    };
+    auto copy_weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < W_PASS; ++i) copy_weight(i);
+    };
+    // lane (l32, lh) of a fragment holds chunk 2*kk + lh of row l32; the chunks of kk 0..3 are those of
+    // kk = 0 with bits 1 and 2 of the chunk number flipped
+    const int chunk = (lh ^ (l32 & 7) ^ (l32 >> 3 & 1)) << 4;
+    int to = (TB0 * 32 + l32) * 128 + chunk, wo = TL::W_RING + (wn * 64 + l32) * 128 + chunk;
+    bf16x8 wf[2][WB], tf[PF];
+#define MOE_TOK(to_, q_) (*reinterpret_cast<const bf16x8 *>(smem + ((to_) ^ (((q_) / NBT) * 32)) + ((q_) % NBT) * 4096))
+#define MOE_WGT(wo_, kk_, b_) (*reinterpret_cast<const bf16x8 *>(smem + ((wo_) ^ ((kk_) * 32)) + (b_) * 4096))
+
+    copy_tokens();                                            // stage 0
+    copy_weights();
+    if (nk > 1) {                                             // stage 1
+        copy_weights();
+#pragma unroll
+        for (int c = 0; c < NPRE; ++c) copy_token(c);
+    }
+    if (nk > 1) MOE_WAIT_VMCNT(W_PASS + NPRE);
+    else MOE_WAIT_VMCNT(0);
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int b = 0; b < WB; ++b) wf[0][b] = MOE_WGT(wo, 0, b);
+#pragma unroll
+    for (int q = 0; q < PF; ++q) tf[q] = MOE_TOK(to, q);
+    __builtin_amdgcn_sched_barrier(0);
+
+    int ws = 0;                                               // weight slot of this step
+    // Step s issues the token copies of step s+1 and the weight copies of step s+2, spread over its groups.
+    // LEFT: steps after this one, 0, 1 or (2) more
+    auto step = [&](auto left_) __attribute__((always_inline)) {
+        constexpr int LEFT = decltype(left_)::value;
+        const int to_next = to ^ TL::A_STAGE;
+        ws = ws == 2 ? 0 : ws + 1;
+        const int wo_next = ws == 0 ? wo - 2 * TL::W_STAGE : wo + TL::W_STAGE;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int kk = q / NBT, m = q % NBT;
+#pragma unroll
+            for (int b = 0; b < WB; ++b)
+                acc[m][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1][b], tf[q % PF], acc[m][b], 0, 0, 0);
+            if (q + PF < NQ) tf[q % PF] = MOE_TOK(to, q + PF);
+            if (m == 0 && kk + 1 < NKK) {                     // the next 16 columns' weights
+#pragma unroll
+                for (int b = 0; b < WB; ++b) wf[(kk + 1) & 1][b] = MOE_WGT(wo, kk + 1, b);
+            }
+            // (issued in one go the copies would hold the wavefront up until the memory pipeline has taken
+            // them all); the first of step s+1's token copies follow this step's meeting
+            if (q <= QB) {
+#pragma unroll
+                for (int c = NPRE + q * CPG; c < NPRE + (q + 1) * CPG; ++c) {
+                    if (c < A_PASS) {
+                        if (LEFT >= 1) copy_token(c);
+                    } else if (c < A_PASS + W_PASS) {
+                        if (LEFT >= 2) copy_weight(c - A_PASS);
+                    }
+                }
+            }
+            if (LEFT >= 1) {
+                if (q == QB) {
+                    // every fragment of this stage has been requested: once they are here, and the next
+                    // stage has landed, all wavefronts meet; then this stage may be overwritten
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    if (LEFT >= 2) MOE_WAIT_VMCNT(W_PASS);
+                    else MOE_WAIT_VMCNT(0);
+                    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+                    for (int b = 0; b < WB; ++b) wf[0][b] = MOE_WGT(wo_next, 0, b);
+#pragma unroll
+                    for (int j = 0; j <= QB - (NQ - PF); ++j) tf[j] = MOE_TOK(to_next, j);
+                }
+                if (q > QB) tf[q - (NQ - PF)] = MOE_TOK(to_next, q - (NQ - PF));
+                if (LEFT >= 2 && q >= QB) {
+#pragma unroll
+                    for (int c = (q - QB) * CPG; c < (q - QB + 1) * CPG && c < NPRE; ++c) copy_token(c);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        to = to_next;
+        wo = wo_next;
+    };
+    for (int s = 0; s + 2 < nk; ++s) step(std::integral_constant<int, 2>{});
+    if (nk > 1) step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 0>{});
+    MOE_WAIT_VMCNT(0);                                        // (nothing is in flight; cheap insurance for the LDS reuse below)
+#undef MOE_TOK
+#undef MOE_WGT
+
+    // ---- epilogue: the output tile is staged in LDS and leaves as whole rows (see gemm_tile).  Lane
+    // (l32, lh) holds, for token l32 of a block, weight rows 8*j + 4*lh .. +3 in registers 4*j .. 4*j+3.
+    const int wcol = wn * (SH::COLS / 4);                     // this wavefront's first column inside the slab
+    const int tid = t.tid;
+    if constexpr (SH::SPLITK) {
+        constexpr int NBT0 = (TB + 1) / 2;                    // blocks of the first half of the tile's rows
+        constexpr int ROW_B = SH::COLS * 4, CPR = ROW_B / 16;
+        constexpr int PARTS = (2 * NBT0 * 32 * ROW_B + TL::LDS_BYTES - 1) / TL::LDS_BYTES;
+        constexpr int NBP = (NBT0 + PARTS - 1) / PARTS;       // row blocks of each half that leave together
+        static_assert(2 * NBP * 32 * ROW_B <= TL::LDS_BYTES, "a part of the output tile must fit the LDS of the rings");
+        auto stage_at = [&](int r, int byte) __attribute__((always_inline)) {
+            return smem + r * ROW_B + ((((byte >> 4) ^ ((r & (CPR / 2 - 1)) << 1))) << 4) + (byte & 15);
+        };
+        unsigned char *const part_out = g.out + (size_t)t.kh * g.split_stride;
+        const size_t out_pitch = (size_t)n_out * 4;
+#pragma unroll
+        for (int part = 0; part < PARTS; ++part) {
+            const int m0 = part * NBP;
+            __syncthreads();
+#pragma unroll
+            for (int m = m0; m < m0 + NBP && m < NBT; ++m) {
+                const int r = ((TB0 ? NBP : 0) + m - m0) * 32 + l32;
+#pragma unroll
+                for (int b = 0; b < WB; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        *reinterpret_cast<f32x4 *>(stage_at(r, (wcol + b * 32 + j * 8 + lh * 4) * 4)) =
+                            f32x4{acc[m][b][4 * j], acc[m][b][4 * j + 1], acc[m][b][4 * j + 2], acc[m][b][4 * j + 3]};
+            }
+            __syncthreads();
+            for (int c = tid; c < 2 * NBP * 32 * CPR; c += SH::THREADS) {
+                const int r = c / CPR, ch = c % CPR;
+                const int half = r / (NBP * 32), in_half = m0 * 32 + r % (NBP * 32);
+                const int trow = half * (NBT0 * 32) + in_half;
+                const int col = ct * SH::COLS + ch * 4;
+                if ((half || in_half < NBT0 * 32) && trow < rows && col < n_out) {
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(stage_at(r, ch * 16));
+                    u32x4 *dst = reinterpret_cast<u32x4 *>(part_out + (size_t)(tile.row0 + trow) * out_pitch + (size_t)col * 4);
+                    if (g.nt_out) __builtin_nontemporal_store(v, dst);
+                    else *dst = v;
+                }
+            }
+        }
+    } else {
+        constexpr int ROW_B = SH::COLS * 2, CPR = ROW_B / 16;
+        static_assert(TB * 32 * ROW_B <= TL::LDS_BYTES, "output tile must fit the LDS of the rings");
+        auto stage_at = [&](int r, int byte) __attribute__((always_inline)) {
+            return smem + r * ROW_B + ((((byte >> 4) ^ ((r & (CPR / 2 - 1)) << 1))) << 4) + (byte & 15);
+        };
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NBT; ++m) {
+            const int r = (TB0 + m) * 32 + l32;
+            if constexpr (SWIGLU) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float a[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float gt = acc[m][0][4 * j + v], up = acc[m][1][4 * j + v];
+                        a[v] = gt / (1.f + __expf(-gt)) * up;
+                    }
+                    uint2 o;
+                    o.x = pack_bf16x2(a[0], a[1]);
+                    o.y = pack_bf16x2(a[2], a[3]);
+                    *reinterpret_cast<uint2 *>(stage_at(r, (wcol + j * 8 + lh * 4) * 2)) = o;
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < WB; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        uint2 o;
+                        o.x = pack_bf16x2(acc[m][b][4 * j], acc[m][b][4 * j + 1]);
+                        o.y = pack_bf16x2(acc[m][b][4 * j + 2], acc[m][b][4 * j + 3]);
+                        *reinterpret_cast<uint2 *>(stage_at(r, (wcol + b * 32 + j * 8 + lh * 4) * 2)) = o;
+                    }
+            }
+        }
+        __syncthreads();
+        const size_t out_pitch = (size_t)n_out * 2;
+        for (int c = tid; c < rows * CPR; c += SH::THREADS) {
+            const int r = c / CPR, ch = c % CPR;
+            const int col = ct * SH::COLS + ch * 8;
+            if (col < n_out) {
+                const u32x4 v = *reinterpret_cast<const u32x4 *>(stage_at(r, ch * 16));
+                u32x4 *dst = reinterpret_cast<u32x4 *>(g.out + (size_t)(tile.row0 + r) * out_pitch + (size_t)col * 2);
+                if (g.nt_out) __builtin_nontemporal_store(v, dst);
+                else *dst = v;
+            }
+        }
+    }
+}
+
+// TB: 32-row blocks of the tile.  The first four wavefronts take the first (TB+1)/2 of them, the others the
+// rest: a compute unit's four matrix pipes each hold one wavefront of either half.
+template <class SH, int TB>
+__device__ __forceinline__ void gemm_tile_tall16(const GemmArgs &g, const Item &item, unsigned char *smem)
+{
+    constexpr int ES = 2;
+    int tid_opaque = threadIdx.x;                             // (see gemm_tile)
+    asm volatile("" : "+v"(tid_opaque));
+    const size_t row_bytes = (size_t)g.K * ES;
+    const int ct = SH::SPLITK ? item.ct >> 1 : item.ct, kh = SH::SPLITK ? item.ct & 1 : 0;
+    const int nk = (int)(row_bytes / GM_STEP_BYTES) / (SH::SPLITK ? 2 : 1);
+    // Workgroups that share weight and token lines through L2 start at the same column, experts (XCDs) at different ones:
+    // with a start per workgroup the Mixtral gate/up launch fetched 8.0 GB, with this 3.9.
+    const int koff = (int)((long)(item.tile.expert * 5 % g.k_groups) * nk / g.k_groups);
+    const int wave = __builtin_amdgcn_readfirstlane(tid_opaque >> 6);
+    const Tall16Args t{g, item.tile, smem, tid_opaque, tid_opaque & 63, wave, ct, kh, nk, koff,
+                         row_bytes, (size_t)kh * nk * GM_STEP_BYTES};
+    constexpr int NBT0 = (TB + 1) / 2, NBT1 = TB / 2;
+    if (wave < 4) tall16_wave<SH, TB, NBT0, 0>(t);
+    else tall16_wave<SH, TB, NBT1, NBT0>(t);
+}
+
 }  // namespace
 }  // namespace moe

@@ -1,5 +1,6 @@
-"""Tall tiles of the fp8 grouped GEMMs: every height of eight row blocks and more, ragged and whole, experts of
-several tiles, the shortest K loop they take and one past the first register of weight scales, a ragged last slab."""
+"""Tall tiles of the grouped GEMMs.  fp8: every height of eight row blocks and more, ragged and whole, experts of
+several tiles, the shortest K loop they take and one past the first register of weight scales, a ragged last slab.
+bf16: experts of three tiles and more, odd and even numbers of 32-row blocks, one K step and up, K in halves."""
 import pytest
 import torch
 
@@ -59,3 +60,64 @@ def test_tall_fp8_tiles(rows, H, I, down_wide):
         # grid fixed by the largest of them (2^-14 of the sum of magnitudes measured, in gemm_tile as well)
         bound = ref.abs() * 2.0 ** -8 + (got.abs() @ w.abs()) * 2.0 ** -13
         assert ((y[lo:hi].double() - ref).abs() <= bound).all(), f"down, expert {e} of {hi - lo} rows"
+
+
+@pytest.mark.parametrize("H, I", [
+    (64, 8192), (128, 8192), (192, 8256), (1024, 8192),          # gate/up: 1, 2, 3 and 16 K steps, a ragged last slab
+    (16384, 64), (16448, 192),                                   # down: 1 and 3 K steps, a ragged last slab
+])
+def test_tall_bf16_tiles(H, I):
+    rows = [1825, 1024, 700, 600, 513, 257, 40, 0]               # eight, four and three tiles, of 5 to 8 blocks of 32 rows
+    E, T = len(rows), sum(rows)
+    cfg = moe.MoEConfig(T, H, I, E, 1, 0, 1, 1, 1, 1, 0, 1.0, 0, 0, 0)
+    which = "gateup" if I > H else "down"
+    plan = moe.moe_gemm_plan(cfg, which)
+    assert plan["tile_rows"] == 256 and plan["wavefronts"] == 8 and plan["k_split"] == 1
+    gen = torch.Generator("cuda").manual_seed(H + I)
+    ids = torch.repeat_interleave(torch.arange(E), torch.tensor(rows)).cuda()[torch.randperm(T, generator=gen, device="cuda")]
+    offsets, pair, inv, tiles, sched = moe.moe_permute(cfg, ids.to(torch.int32).view(T, 1))
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    off = offsets.tolist()
+    # one bf16 rounding (2^-9 of the value) of fp32 sums (2^-24 a term, of the sum of magnitudes)
+    if which == "gateup":
+        x, w1 = draw(T, H).bfloat16(), (draw(E, 2 * I, H) * H ** -0.5).bfloat16()
+        act, _ = moe.moe_grouped_gemm_swiglu(cfg, x, None, w1, None, pair, tiles, sched)
+        for e in range(E):
+            lo, hi = off[e], off[e + 1]
+            xe, w = x[pair[lo:hi].long()].double(), w1[e].double().t()
+            gu = xe @ w
+            ref = torch.nn.functional.silu(gu[:, :I]) * gu[:, I:]
+            slack = (xe.abs() @ w.abs()).max() ** 2 * 2.0 ** -20 if hi > lo else 0.0
+            assert ((act[lo:hi].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + slack).all(), f"expert {e}"
+    else:
+        act, w2 = draw(T, I).bfloat16(), (draw(E, H, I) * I ** -0.5).bfloat16()
+        y = moe.moe_grouped_gemm_down(cfg, act, None, w2, None, tiles, sched)
+        for e in range(E):
+            lo, hi = off[e], off[e + 1]
+            a, w = act[lo:hi].double(), w2[e].double().t()
+            ref = a @ w
+            assert ((y[lo:hi].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + (a.abs() @ w.abs()) * 2.0 ** -20).all(), f"expert {e}"
+
+
+@pytest.mark.parametrize("T", [700, 1825])
+def test_tall_bf16_tiles_with_k_in_halves(T):
+    """Every token goes to both experts: three (eight) tiles each in the forward's K-split down projection."""
+    H, I, E = 576, 4096, 2
+    cfg = moe.MoEConfig(T, H, I, E, 2, 0, 1, 1, 1, 1, 0, 1.0, 0, 0, 0)
+    assert moe.moe_gemm_plan(cfg, "down")["k_split"] == 2
+    gen = torch.Generator("cuda").manual_seed(T)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    x, router = draw(T, H).bfloat16(), draw(E, H) * H ** -0.5
+    w1, w2 = (draw(E, 2 * I, H) * H ** -0.5).bfloat16(), (draw(E, H, I) * I ** -0.5).bfloat16()
+    out = moe.moe_forward(cfg, x, None, router, None, w1, None, w2, None)
+    xd = x.double()
+    w = torch.softmax(xd @ router.double().t(), dim=1)
+    ref, mag = torch.zeros_like(xd), torch.zeros_like(xd)
+    for e in range(E):
+        gu = xd @ w1[e].double().t()
+        act = (torch.nn.functional.silu(gu[:, :I]) * gu[:, I:]).bfloat16().double()
+        ref += w[:, e:e + 1] * (act @ w2[e].double().t())
+        mag += w[:, e:e + 1] * (act.abs() @ w2[e].double().abs().t())
+    # bf16 rows (2^-9 each of what they add) and a bf16 output; activations whose rounding flips (2^-8 of one of 4096 terms)
+    bound = ref.abs() * 2.0 ** -8 + mag * 2.0 ** -9
+    assert ((out.double() - ref).abs() <= bound).all()
