@@ -6,8 +6,12 @@ namespace moe {
 namespace {
 
 constexpr int PM_THREADS = 1024;
+// A handful of pairs over few experts: four wavefronts start, count and meet sooner than sixteen (32 pairs, 8 experts:
+// 5.4 -> 4.4 us).  The ranking of more experts than this wants the threads.
+constexpr int PM_FEW_THREADS = 256, PM_FEW_PAIRS = 256, PM_FEW_EXPERTS = 64;
 
-__global__ __launch_bounds__(PM_THREADS) void permute_kernel(const int32_t *__restrict__ ids, int P, int E,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void permute_kernel(const int32_t *__restrict__ ids, int P, int E,
                                                              int e_first, int tile_rows, int max_tiles,
                                                              int32_t *__restrict__ offsets,
                                                              int32_t *__restrict__ sorted_pair,
@@ -16,7 +20,7 @@ __global__ __launch_bounds__(PM_THREADS) void permute_kernel(const int32_t *__re
                                                              int32_t *__restrict__ sched)
 {
     extern __shared__ int lds[];
-    permute_block<PM_THREADS>(ids, P, E, e_first, tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched, lds,
+    permute_block<THREADS>(ids, P, E, e_first, tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched, lds,
                               (int)blockIdx.x, (int)gridDim.x);
 }
 
@@ -28,9 +32,15 @@ int launch_permute(const moe_config &c, int tile_rows, int max_tiles, const int3
 {
     const int P = c.T * c.top_k;
     const int el = local_experts(c);
+    if (P <= PM_FEW_PAIRS && el <= PM_FEW_EXPERTS) {
+        hipLaunchKernelGGL(permute_kernel<PM_FEW_THREADS>, dim3(1), dim3(PM_FEW_THREADS),
+                           sizeof(int) * permute_lds_ints(PM_FEW_THREADS, el), s, ids, P, el, c.local_expert_offset,
+                           tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched);
+        return check_launch();
+    }
     const size_t lds = sizeof(int) * permute_lds_ints(PM_THREADS, el);
     const int wgs = min(PM_MAX_WGS, max(1, ceil_div(P, PM_SLICE)));
-    hipLaunchKernelGGL(permute_kernel, dim3(wgs), dim3(PM_THREADS), lds, s, ids, P, el, c.local_expert_offset,
+    hipLaunchKernelGGL(permute_kernel<PM_THREADS>, dim3(wgs), dim3(PM_THREADS), lds, s, ids, P, el, c.local_expert_offset,
                        tile_rows, max_tiles,
                        offsets, sorted_pair, inv, tiles, sched);
     return check_launch();
