@@ -801,9 +801,11 @@ struct ShapesFor {
     static constexpr int DW = 2;
     using Wide = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8>;
     using Narrow = Shape<MB_MAX, 4, DA, 3, SWIGLU, FP8>;
-    // Low tiles with a long K: the copies of a step are waited for in the order they were issued, so what is in
-    // flight is DA + 1 stages whatever DW says, and a launch of fewer workgroups than compute units (three Mixtral
-    // tokens: 192) streamed at 5.7 TB/s with 32 KiB each; with 64 KiB 6.6 (down projection 124 -> 107 us).
+    // Low tiles with a long K, in a launch of fewer workgroups than compute units: the copies of a step are waited for in
+    // the order they were issued, so what is in flight is DA + 1 stages whatever DW says, and one workgroup per compute
+    // unit (three Mixtral tokens: 192) streamed at 5.7 TB/s with 32 KiB each; with 64 KiB 6.6 (down projection 124 ->
+    // 107 us).  Where two of the small workgroups share a compute unit they are the faster ones: 40 32-row tiles of
+    // 2560 x 1408, 163 us a layer against 181 with the deep rings, which fill the LDS with one.
     using NarrowDeep = Shape<MB_MAX, 4, MB_MAX <= 2 ? 4 : DA, MB_MAX <= 2 ? 5 : 3, SWIGLU, FP8>;
     using Wide4 = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8, SWIGLU ? 2 : 4>;
     using WideSplit = Shape<MB_MAX, 8, DA, DW, false, false, 2, true>;
@@ -826,7 +828,8 @@ int launch_for_rows(const GemmArgs &g, const moe_tile *tiles, const int32_t *sch
         return MOE_ERR_UNSUPPORTED;
     case GEMM_NARROW:
         if constexpr (!(FP8 && SWIGLU) && MB_MAX <= 2)
-            if (g.K * (FP8 ? 1 : 2) / GM_STEP_BYTES >= kLongK)
+            if (g.K * (FP8 ? 1 : 2) / GM_STEP_BYTES >= kLongK &&
+                (long)est_tiles * ceil_div(g.n_out, SF::NarrowDeep::COLS) <= kComputeUnits)
                 return launch_shape<typename SF::NarrowDeep>(g, tiles, sched, max_tiles, est_tiles, s);
         if constexpr (!(FP8 && SWIGLU))
             return launch_shape<typename SF::Narrow>(g, tiles, sched, max_tiles, est_tiles, s);

@@ -160,13 +160,14 @@ inline int expected_tiles(const moe_config &c)
 constexpr int kLongK = 16;
 
 // Whether XCD r works through work range r, whole tiles only, or through one of eight equal parts of the items
-// (see gemm_items): whole ranges when an XCD has at most eight tiles and they are 64 rows or taller.  Token rows of
-// lower tiles are too few to matter to an L2, while ranges of whole tiles leave XCDs idle: three Mixtral tokens hit
-// six experts, six ranges (gate/up 269 -> 205 us with equal parts); fp8 share of 26 32-row tiles, three or four a
-// range, down 66 -> 59 us.  64-row tiles of 60 experts: gate/up 39 us in whole ranges, 45 in equal parts.
+// (see gemm_items): whole ranges when an XCD has at most eight tiles, unless they are low and at most four.  Token rows
+// of low tiles are too few to matter to an L2, while ranges of a few whole tiles leave XCDs idle: three Mixtral tokens
+// hit six experts, six ranges (gate/up 269 -> 205 us with equal parts); fp8 share of 26 32-row tiles, three or four a
+// range, down 66 -> 59 us.  With 60 32-row tiles equal parts were 3 % slower, with 60 64-row tiles 15 % (39 -> 45 us).
 inline bool gemm_whole_ranges(int mb_max, int k_steps, int est_tiles)
 {
-    return est_tiles <= 8 * MOE_WORK_RANGES && (mb_max >= 4 || k_steps < kLongK);
+    const bool few_low = mb_max <= 2 && est_tiles <= 4 * MOE_WORK_RANGES && k_steps >= kLongK;
+    return est_tiles <= 8 * MOE_WORK_RANGES && !few_low;
 }
 
 // Tile height: the smallest of 16..256 that holds an expert's rows with a binomial safety

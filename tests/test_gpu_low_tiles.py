@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("rows, H, I", [
     ([1], 64, 64), ([2, 0, 1, 0, 0, 3], 128, 320), ([1, 1, 0, 1, 1, 1, 1], 1024, 4160), ([16, 15, 1], 576, 2048),
-    ([17, 32, 1, 9], 448, 1024), ([12] * 40, 256, 192),
+    ([17, 32, 1, 9], 448, 1024), ([12] * 40, 256, 192), ([3, 1, 2], 1088, 256),
 ])
 def test_low_tiles_of_few_experts(rows, H, I):
     E, T = len(rows), sum(rows)
