@@ -19,7 +19,8 @@
 //    DW stages in flight); the token rows (x gathered through the sorted pair list, or act) are
 //    shared by all wavefronts and land in a second ring DA steps ahead.  Physical 16-byte chunk pc
 //    of LDS row r holds logical chunk pc ^ (r & 7) (applied on the global-address side of the
-//    copy), which keeps the 16-byte MFMA fragment reads free of bank conflicts.
+//    copy), which keeps the 16-byte MFMA fragment reads of the bf16 tiles free of bank conflicts (those of
+//    the fp8 tiles meet in pairs; the order of moe_gemm_tall.hpp avoids it, here it gained nothing).
 //  * One K step is 128 bytes of every row: 64 bf16 elements (two v_mfma_f32_16x16x32_bf16) or
 //    128 fp8 elements (one v_mfma_f32_16x16x128_f8f6f4, exactly one 128-wide scale block).  The
 //    weights are the row operand, so the accumulator of lane l holds 4 consecutive output
@@ -39,6 +40,9 @@
 //    row-block count), so an expert with 140 tokens costs 9-10 blocks of 16, not 256 rows.
 //  * Workgroups start their K loops at different columns when the row stride is a multiple of
 //    4 KiB (see k_groups_for).
+//
+// Tall tiles of fp8 launches, and of bf16 experts with several of them, have K loops of their own
+// (moe_gemm_tall.hpp).
 //
 // The tile list arrives as a schedule of eight work ranges, tallest tiles first (moe_permute);
 // workgroups are numbered so that each XCD (own L2) works through one range: the token rows of
