@@ -314,7 +314,7 @@ MfmaGrid mfma_grid(const moe_config &c)
     g.use = c.E > RT_FEW && !single_launch_shape(c);
     if (!g.use) return g;
     g.few = c.T < RM_MANY_TOKENS;
-    g.tiles_t = ceil_div(c.T, g.few ? 64 : 128);
+    g.tiles_t = c.T > 0 ? ceil_div(c.T, g.few ? 64 : 128) : 1;   // (size queries of no tokens come here too)
     g.tiles_e = ceil_div(c.E, g.few ? 128 : 256);
     const int chunks = c.H / RM_BK;
     int want = ceil_div(256, g.tiles_t * g.tiles_e);
