@@ -648,7 +648,8 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
             if constexpr (SH::TALL && NB >= SH::TALL_MIN) {
                 // (down-projection items of half width stay here)
                 if constexpr (SH::FP8) {
-                    if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0) {   // K in whole blocks of four steps, see there
+                    // K in whole blocks of four steps, whose scales are copied 16 bytes at a time, see there
+                    if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0 && ((uintptr_t)g.a_scale & 15) == 0) {
                         if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
                         else gemm_tile_tall8<SH, NB, false>(g, item, smem);
                         return false;

@@ -14,7 +14,7 @@
 //    the requests of one 4-byte copy per row and step (those were 30 % of all L2 requests);
 //  * LDS row r holds 16-byte chunk c at place c ^ (r & 7) ^ (r >> 3 & 1): with c ^ (r & 7) alone, half of the LDS
 //    cycles of the fp8 fragment reads were bank conflicts.
-// The sums see the same terms in the same order as in gemm_tile.  Measured on the 32-expert share of the
+// The sums see the same terms in the same order as in gemm_tile (rotated starts apart: whole blocks of four steps).  Measured on the 32-expert share of the
 // DeepSeek-shaped layer: 16384 tokens, gate/up 612 -> 498 us, down 346 -> 317; 4096 tokens, 224 -> 218 and 133 -> 121.
 // Fetching the lines of three steps ahead into L2 as well was slower (498 -> 553): the requests cost more than the
 // latency they hide.  Needs K in whole blocks of four steps (the 16-byte scale copies); other tiles and the half-width
