@@ -163,6 +163,11 @@ struct Shape {
     static constexpr int TALL_MIN = FP8 ? 8 : 9, TALL_COUNT = 3;
     static constexpr int TALL_BYTES = !TALL ? 0 : FP8 ? 4 * 256 * 128 + 3 * 256 * 16 : 5 * 256 * 128;
     static constexpr int LDS_BYTES = RING_BYTES > TALL_BYTES ? RING_BYTES : TALL_BYTES;
+    // LDS of gemm_tile's staged output tile of nb row blocks (it lies over the token ring, from its start)
+    static constexpr int staged_bytes(int nb)
+    {
+        return ((SWIGLU && FP8) ? NW * nb * 16 * 4 : 0) + nb * 16 * COLS * ((SWIGLU && FP8) ? 1 : 2);
+    }
     static_assert(DW >= DA && DA >= 1, "weights are copied at least as far ahead as token rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
     // half-width items (see gemm_tile): wide workgroups of launches in whole ranges only (gemm_whole_ranges); the
@@ -178,13 +183,37 @@ struct Item {
     int ct, half, work;
 };
 
+// Whether an item goes through one of the tall-tile loops (moe_gemm_tall.hpp).  Half-width items stay with gemm_tile.
+template <class SH>
+__host__ __device__ __forceinline__ bool takes_tall_loop(const GemmArgs &g, const Item &item)
+{
+    if constexpr (!SH::TALL) {
+        return false;
+    } else {
+        if (item.half || ceil_div(item.tile.rows, 16) < SH::TALL_MIN) return false;
+        // fp8: K in whole blocks of four steps, whose scales are copied 16 bytes at a time
+        if constexpr (SH::FP8) return g.K % (4 * GM_STEP_BYTES) == 0 && ((uintptr_t)g.a_scale & 15) == 0;
+        else return item.tile.count >= SH::TALL_COUNT;
+    }
+}
+
+// Whether gemm_tile<SH, NB, HALF> requests the first weight stages of the item after its own.  Both have to use the
+// weight ring of gemm_tile: a tall loop lays out the same LDS in another way, waits for the copies of its own wavefront
+// only, and would start its copies while those of another wavefront may still land on top of them.
+template <class SH, int NB, bool HALF>
+__host__ __device__ __forceinline__ bool requests_next(const GemmArgs &g, const Item &next, bool has_next)
+{
+    if constexpr (HALF || SH::SPLITK || SH::staged_bytes(NB) > SH::A_RING_BYTES) return false;
+    else return has_next && next.half == 0 && !takes_tall_loop<SH>(g, next);
+}
+
 // Everything after the (tile, column slab) decision, instantiated per active row-block count NB.
 // A workgroup may work through several items in a row.  `next` (if has_next) is the item it takes
-// after this one: when both are whole-slab items and the staged output tile of this one leaves the
-// weight ring alone, the first weight stages of `next` are requested before this item's epilogue,
-// so that the latency of their trip from HBM passes while the output is written; the call then
-// returns true and the next call is told so (`prefetched`: its weight copies of stages 0..DW-1
-// are already under way).
+// after this one: when both are whole-slab items of this loop and the staged output tile of this one
+// leaves the weight ring alone (requests_next), the first weight stages of `next` are requested before
+// this item's epilogue, so that the latency of their trip from HBM passes while the output is written;
+// the call then returns true and the next call is told so (`prefetched`: its weight copies of stages
+// 0..DW-1 are already under way).
 template <class SH, int NB, bool HALF>
 __device__ __forceinline__ bool gemm_tile(const GemmArgs &g, const Item item, const Item next, const bool has_next,
                                           const bool prefetched, unsigned char *smem)
@@ -473,10 +502,9 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs &g, const Item item, co
     // Every copy of this item has landed (the last step waited for its own, and nothing was issued
     // after those).  The output tile is staged over the token ring; when it stays clear of the
     // weight ring, this wavefront's first weight stages of the next item go out now.
-    constexpr int STAGED_BYTES = ((SWIGLU && FP8) ? NW * NB * 16 * 4 : 0) + NB * 16 * SH::COLS * ((SWIGLU && FP8) ? 1 : 2);
-    bool gave_next = false;
-    if constexpr (!HALF && !SH::SPLITK && STAGED_BYTES <= SH::A_RING_BYTES) {
-        if (has_next && next.half == 0) {
+    const bool gave_next = requests_next<SH, NB, HALF>(g, next, has_next);
+    if constexpr (!HALF && !SH::SPLITK && SH::staged_bytes(NB) <= SH::A_RING_BYTES) {
+        if (gave_next) {
             const unsigned char *nw_ptr[GM_W_COPIES];
             weight_ptrs(next.tile.expert, next.ct * SH::COLS + wave * SLAB, nw_ptr);
             const int nkoff = (int)((long)(next.work % g.k_groups) * nk / g.k_groups);
@@ -484,7 +512,6 @@ __device__ __forceinline__ bool gemm_tile(const GemmArgs &g, const Item item, co
 #pragma unroll
             for (int t = 0; t < DW; ++t)
                 if (t < nk) MOE_COPY_WEIGHTS_OF(t, nw_ptr, nkoff, nshare)
-            gave_next = true;
         }
     }
     if (!gave_next) MOE_WAIT_VMCNT(0);                        // nothing is in flight any more; cheap insurance for the LDS reuse below
@@ -646,16 +673,10 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
         constexpr int NEXT = NB + 1;
         if (nb <= NB) {
             if constexpr (SH::TALL && NB >= SH::TALL_MIN) {
-                // (down-projection items of half width stay here)
-                if constexpr (SH::FP8) {
-                    // K in whole blocks of four steps, whose scales are copied 16 bytes at a time, see there
-                    if (!item.half && g.K % (4 * GM_STEP_BYTES) == 0 && ((uintptr_t)g.a_scale & 15) == 0) {
-                        if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
-                        else gemm_tile_tall8<SH, NB, false>(g, item, smem);
-                        return false;
-                    }
-                } else if (!item.half && item.tile.count >= SH::TALL_COUNT) {
-                    gemm_tile_tall16<SH, (NB + 1) / 2>(g, item, smem);
+                if (takes_tall_loop<SH>(g, item)) {            // (`prefetched` is never set for it: requests_next)
+                    if constexpr (!SH::FP8) gemm_tile_tall16<SH, (NB + 1) / 2>(g, item, smem);
+                    else if (item.tile.count > (SH::SWIGLU ? 2 : 1)) gemm_tile_tall8<SH, NB, true>(g, item, smem);
+                    else gemm_tile_tall8<SH, NB, false>(g, item, smem);
                     return false;
                 }
             }
@@ -692,39 +713,47 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
 // done: with 2 / 4 / 8 items per workgroup the gate/up GEMM of a 4096-token DeepSeek-shaped prefill took
 // +2 / +8 / +21 % (the hardware's hand-out of fresh workgroups balances tiles of unequal height, a fixed
 // share per workgroup does not), with or without the prefetch.
-template <class SH>
-__device__ __forceinline__ void gemm_items(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched,
-                                           int col_tiles, int whole_ranges, int round_slots, int block,
-                                           int nblocks, unsigned char *smem)
-{
-    const int part = block % MOE_WORK_RANGES;
-    int first, items;
-    if (whole_ranges) {
-        first = sched[1 + part] * col_tiles;
-        items = sched[2 + part] * col_tiles - first;
-    } else {
-        const int total = sched[0] * col_tiles;
-        const int per = ceil_div(total, MOE_WORK_RANGES);
-        first = part * per;
-        items = min(per, total - first);
+struct ItemWalk {
+    const moe_tile *tiles;
+    int col_tiles, first, items, halved, nchunks, slots;
+    bool zigzag;
+
+    template <class SH>
+    __host__ __device__ __forceinline__ static ItemWalk of_part(const moe_tile *tiles, const int32_t *sched, int col_tiles,
+                                                                int whole_ranges, int round_slots, int part)
+    {
+        ItemWalk k{};
+        k.tiles = tiles;
+        k.col_tiles = col_tiles;
+        if (whole_ranges) {
+            k.first = sched[1 + part] * col_tiles;
+            k.items = sched[2 + part] * col_tiles - k.first;
+        } else {
+            const int total = sched[0] * col_tiles;
+            const int per = ceil_div(total, MOE_WORK_RANGES);
+            k.first = part * per;
+            k.items = per < total - k.first ? per : total - k.first;
+        }
+        // Order inside a long part: alternating between its front and its back in chunks of col_tiles
+        // items (tall tile, short tile, tall, ...) instead of tallest-first.  Tall tiles spend their
+        // time on LDS and the matrix cores, short ones on the weight stream, and a mix of both running
+        // side by side is faster than all tall tiles together: gate/up GEMM -4..5 % on the DeepSeek-shaped
+        // prefills; the down GEMM -12 % when the tallest tiles are full height (hot experts), but +5 % when
+        // every tile is low, where tallest-first only shortens the tail - so it alternates only when the
+        // tallest tile of the list (its first record) has more than 128 rows.
+        k.zigzag = !whole_ranges && (SH::SWIGLU || tiles[0].rows > 128);
+        k.nchunks = ceil_div(k.items, col_tiles);
+        // A last round that would fill at most half of the XCD's workgroup slots is handed out as
+        // half-width items, two per column slab.
+        const int rest = k.items % round_slots;
+        k.halved = (SH::HALF_ITEMS && whole_ranges && rest > 0 && 2 * rest <= round_slots) ? rest : 0;
+        k.slots = k.zigzag ? k.nchunks * col_tiles : k.items + k.halved;
+        return k;
     }
-    const int stride = nblocks / MOE_WORK_RANGES;
-    // Order inside a long part: alternating between its front and its back in chunks of col_tiles
-    // items (tall tile, short tile, tall, ...) instead of tallest-first.  Tall tiles spend their
-    // time on LDS and the matrix cores, short ones on the weight stream, and a mix of both running
-    // side by side is faster than all tall tiles together: gate/up GEMM -4..5 % on the DeepSeek-shaped
-    // prefills; the down GEMM -12 % when the tallest tiles are full height (hot experts), but +5 % when
-    // every tile is low, where tallest-first only shortens the tail - so it alternates only when the
-    // tallest tile of the list (its first record) has more than 128 rows.
-    const bool zigzag = !whole_ranges && (SH::SWIGLU || tiles[0].rows > 128);
-    const int nchunks = ceil_div(items, col_tiles);
-    // A last round that would fill at most half of the XCD's workgroup slots is handed out as
-    // half-width items, two per column slab.
-    const int rest = items % round_slots;
-    const int halved = (SH::HALF_ITEMS && whole_ranges && rest > 0 && 2 * rest <= round_slots) ? rest : 0;
-    const int slots = zigzag ? nchunks * col_tiles : items + halved;
-    // the item in slot `slot` of this part (false: the slot is past the end, or a hole of the last, short chunk)
-    auto item_at = [&](int slot, Item &it) __attribute__((always_inline)) -> bool {
+
+    // the item in slot `slot` of the part (false: the slot is past the end, or a hole of the last, short chunk)
+    __host__ __device__ __forceinline__ bool item_at(int slot, Item &it) const
+    {
         if (slot >= slots) return false;
         int pos = slot;
         if (zigzag) {
@@ -745,15 +774,24 @@ __device__ __forceinline__ void gemm_items(const GemmArgs &g, const moe_tile *ti
         it.ct = local / head.count;                            // column slab
         it.tile = tiles[head.first + local % head.count];
         return true;
-    };
-    // The workgroup takes slots b, b + stride, b + 2 stride, ... (neighbouring workgroups are on
-    // neighbouring slots at any time, so the column slabs of a tile still run side by side and share
-    // its token rows through L2; a workgroup that took consecutive slots instead measured +10..15 %).
+    }
+};
+
+// The workgroup takes slots b, b + stride, b + 2 stride, ... of its part (neighbouring workgroups are on
+// neighbouring slots at any time, so the column slabs of a tile still run side by side and share
+// its token rows through L2; a workgroup that took consecutive slots instead measured +10..15 %).
+template <class SH>
+__device__ __forceinline__ void gemm_items(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched,
+                                           int col_tiles, int whole_ranges, int round_slots, int block,
+                                           int nblocks, unsigned char *smem)
+{
+    const ItemWalk walk = ItemWalk::of_part<SH>(tiles, sched, col_tiles, whole_ranges, round_slots, block % MOE_WORK_RANGES);
+    const int stride = nblocks / MOE_WORK_RANGES;
     Item cur{}, nxt{};
     int slot = block / MOE_WORK_RANGES;
-    bool have = item_at(slot, cur), prefetched = false;
-    while (slot < slots) {
-        const bool have_next = item_at(slot + stride, nxt);
+    bool have = walk.item_at(slot, cur), prefetched = false;
+    while (slot < walk.slots) {
+        const bool have_next = walk.item_at(slot + stride, nxt);
         if (have) {
             const int nb = ceil_div(cur.tile.rows, 16);
             prefetched = dispatch_blocks<SH, 1>(nb, g, cur, nxt, have_next, prefetched, smem);
@@ -776,26 +814,37 @@ __global__ __launch_bounds__(SH::THREADS) void grouped_gemm_kernel(GemmArgs g, c
     gemm_items<SH>(g, tiles, sched, col_tiles, whole_ranges, round_slots, (int)blockIdx.x, (int)gridDim.x, smem);
 }
 
+// Grid and item walk of a launch.
+struct LaunchPlan { int col_tiles, round_slots, blocks, whole_ranges; };
+
+template <class SH>
+LaunchPlan launch_plan(const GemmArgs &g, int max_tiles, int est_tiles)
+{
+    LaunchPlan p;
+    p.col_tiles = ceil_div(g.n_out, SH::COLS) * (SH::SPLITK ? 2 : 1);   // split K: two items per column slab
+    // workgroups one XCD runs at once: LDS (160 KiB) and wavefront slots (32) of a compute unit decide it
+    int per_cu = (160 * 1024) / SH::LDS_BYTES;
+    if (per_cu > 32 / SH::NW) per_cu = 32 / SH::NW;
+    p.round_slots = (GM_CUS / GM_XCDS) * (per_cu < 1 ? 1 : per_cu);
+    // a part holds about an eighth of the tiles; the slack (a tile's slabs, and the half-width items
+    // of a last round) keeps the loop in the kernel at one trip, unless hot experts make a range longer than that
+    const int part_slots = (ceil_div(max_tiles, GM_XCDS) + 1) * p.col_tiles + (SH::HALF_ITEMS ? p.round_slots / 2 : 0);
+    p.blocks = part_slots * GM_XCDS;
+    p.whole_ranges = gemm_whole_ranges(SH::MB_MAX, g.K * (SH::FP8 ? 1 : 2) / GM_STEP_BYTES, est_tiles) ? 1 : 0;
+    return p;
+}
+
 template <class SH>
 int launch_shape(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched, int max_tiles, int est_tiles,
                  hipStream_t s)
 {
-    const int col_tiles = ceil_div(g.n_out, SH::COLS) * (SH::SPLITK ? 2 : 1);   // split K: two items per column slab
+    const LaunchPlan p = launch_plan<SH>(g, max_tiles, est_tiles);
     auto kern = grouped_gemm_kernel<SH>;
-    // workgroups one XCD runs at once: LDS (160 KiB) and wavefront slots (32) of a compute unit decide it
-    int per_cu = (160 * 1024) / SH::LDS_BYTES;
-    if (per_cu > 32 / SH::NW) per_cu = 32 / SH::NW;
-    const int round_slots = (GM_CUS / GM_XCDS) * (per_cu < 1 ? 1 : per_cu);
     static DeviceOnce lds_limit_set;                          // the dynamic-LDS limit, once per device
     const int rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), SH::LDS_BYTES);
     if (rc != MOE_OK) return rc;
-    // a part holds about an eighth of the tiles; the slack (a tile's slabs, and the half-width items
-    // of a last round) keeps the loop in the kernel at one trip
-    const int part_slots = (ceil_div(max_tiles, GM_XCDS) + 1) * col_tiles + (SH::HALF_ITEMS ? round_slots / 2 : 0);
-    const int blocks = part_slots * GM_XCDS;
-    const int whole_ranges = gemm_whole_ranges(SH::MB_MAX, g.K * (SH::FP8 ? 1 : 2) / GM_STEP_BYTES, est_tiles) ? 1 : 0;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(SH::THREADS), SH::LDS_BYTES, s, g, tiles, sched, col_tiles, whole_ranges,
-                       round_slots);
+    hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(SH::THREADS), SH::LDS_BYTES, s, g, tiles, sched, p.col_tiles,
+                       p.whole_ranges, p.round_slots);
     return check_launch();
 }
 

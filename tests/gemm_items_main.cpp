@@ -1,0 +1,88 @@
+// Walks the grouped GEMMs' schedules on the host, with the code that the kernels walk them with, and reports what follows
+// what in a workgroup (driven by tests/test_host_item_walk.py).
+//   stdin:  gateup|down bf16|fp8  K n_out max_tiles est_tiles  n  sched[0..15]  n records of eight ints
+//   stdout: items  missing  looped  short_then_tall  requested  requested_tall
+// items: (tile, column slab) items of the launch; missing: column-slab halves that are not handed out exactly once;
+// looped: items that follow another one in their workgroup; short_then_tall: of these, tall-loop items behind one of
+// gemm_tile; requested: items whose weights their predecessor requests; requested_tall: of these, tall-loop items.
+#include <stdio.h>
+#include <string.h>
+
+#include <vector>
+
+#include "moe_gemm_kernel.hpp"
+
+using namespace moe;
+
+namespace {
+
+template <class SH, int NB>
+bool requests(int nb, const GemmArgs &g, const Item &cur, const Item &next, bool has_next)
+{
+    if constexpr (NB > SH::MB_MAX) {
+        return false;
+    } else {
+        if (nb > NB) return requests<SH, NB + 1>(nb, g, cur, next, has_next);
+        return cur.half ? requests_next<SH, NB, true>(g, next, has_next) : requests_next<SH, NB, false>(g, next, has_next);
+    }
+}
+
+template <class SH>
+int walk(const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *sched, int max_tiles, int est_tiles)
+{
+    const LaunchPlan p = launch_plan<SH>(g, max_tiles, est_tiles);
+    const int stride = p.blocks / MOE_WORK_RANGES;
+    std::vector<int> seen((size_t)sched[0] * p.col_tiles * 2);
+    long looped = 0, short_tall = 0, requested = 0, requested_tall = 0;
+    for (int block = 0; block < p.blocks; ++block) {
+        const ItemWalk w = ItemWalk::of_part<SH>(tiles.data(), sched, p.col_tiles, p.whole_ranges, p.round_slots, block % MOE_WORK_RANGES);
+        Item cur{}, nxt{};
+        int slot = block / MOE_WORK_RANGES;
+        bool have = w.item_at(slot, cur);
+        while (slot < w.slots) {
+            const bool have_next = w.item_at(slot + stride, nxt);
+            if (have) {
+                if (cur.half != 2) ++seen[(size_t)cur.work * 2];
+                if (cur.half != 1) ++seen[(size_t)cur.work * 2 + 1];
+            }
+            if (have && have_next) {
+                const bool tall = takes_tall_loop<SH>(g, cur), next_tall = takes_tall_loop<SH>(g, nxt);
+                const bool req = !tall && requests<SH, 1>(ceil_div(cur.tile.rows, 16), g, cur, nxt, true);
+                ++looped;
+                short_tall += !tall && next_tall;
+                requested += req;
+                requested_tall += req && next_tall;
+            }
+            cur = nxt;
+            have = have_next;
+            slot += stride;
+        }
+    }
+    long missing = 0;
+    for (int n : seen) missing += n != 1;
+    printf("%ld %ld %ld %ld %ld %ld\n", (long)seen.size() / 2, missing, looped, short_tall, requested, requested_tall);
+    return 0;
+}
+
+}  // namespace
+
+int main()
+{
+    char which[16], dtype[16];
+    GemmArgs g{};
+    int max_tiles, est_tiles, n;
+    while (scanf("%15s %15s %d %d %d %d %d", which, dtype, &g.K, &g.n_out, &max_tiles, &est_tiles, &n) == 7) {
+        int32_t sched[MOE_SCHED_INTS];
+        for (int &v : sched) if (scanf("%d", &v) != 1) return 1;
+        std::vector<moe_tile> tiles(n);
+        for (moe_tile &t : tiles)
+            for (int i = 0; i < 8; ++i) if (scanf("%d", (int *)&t + i) != 1) return 1;
+        const bool swiglu = !strcmp(which, "gateup"), f8 = !strcmp(dtype, "fp8");
+        const int rc = swiglu ? (f8 ? walk<ShapesFor<16, true, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
+                                    : walk<ShapesFor<16, true, false>::Wide>(g, tiles, sched, max_tiles, est_tiles))
+                              : (f8 ? walk<ShapesFor<16, false, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
+                                    : walk<ShapesFor<16, false, false>::Wide>(g, tiles, sched, max_tiles, est_tiles));
+        if (rc) return rc;
+    }
+    return 0;
+}

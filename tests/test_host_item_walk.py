@@ -1,0 +1,78 @@
+"""The order in which workgroups of the 256-row launches take their items, replayed on the host with the kernels' own
+code (tests/gemm_items_main.cpp): every item is handed out once, and no item requests weights for a successor that a
+tall-tile loop computes, which lays out its LDS in another way."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import test_gpu_tile_handover as handover
+from paper_2602_19128_amd import binding as moe
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def walker(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("walk") / "gemm_items")
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-w",
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2602_19128_amd", "csrc"),
+           os.path.join(ROOT, "tests", "gemm_items_main.cpp"), "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    return exe
+
+
+def schedule(rows, tile_rows):
+    """Schedule header and tile records of experts with `rows` rows, as moe_permute writes them (see include/moe.h)."""
+    off = np.concatenate([[0], np.cumsum(rows)])
+    ranges = [[] for _ in range(8)]
+    for rank, e in enumerate(sorted(range(len(rows)), key=lambda e: (-rows[e], e))):
+        rnd, pos = divmod(rank, 8)
+        ranges[7 - pos if rnd % 2 else pos].append(e)
+    starts, records = [], []
+    for experts in ranges:
+        starts.append(len(records))
+        for e in experts:
+            count, first = -(-rows[e] // tile_rows), len(records)
+            part = -(-(-(-rows[e] // count)) // 16) * 16 if count else 0
+            records += [[e, off[e] + i * part, min(part, rows[e] - i * part), first, count, 0, 0, 0] for i in range(count)]
+    return [len(records)] + starts + [len(records)] + [0] * 6, records
+
+
+def replay(walker, problems):
+    text = []
+    for which, dtype, rows, H, I in problems:
+        cfg = handover.config(which, dtype, rows, H, I)
+        plan = moe.moe_gemm_plan(cfg, which)
+        assert (plan["tile_rows"], plan["wavefronts"], plan["blocks_per_wavefront"]) == (256, 8, 2)
+        sched, records = schedule(rows, 256)
+        K, n_out = (H, I) if which == "gateup" else (I, H)
+        text.append(" ".join(map(str, [which, dtype, K, n_out, moe.moe_max_tiles(cfg), min(sum(rows), len(rows)), len(records)]
+                                 + sched + [v for r in records for v in r])))
+    out = subprocess.run([walker], input="\n".join(text), capture_output=True, text=True, check=True).stdout.splitlines()
+    names = ("items", "missing", "looped", "short_then_tall", "requested", "requested_tall")
+    return [dict(zip(names, map(int, line.split()))) for line in out]
+
+
+def test_handover_cases_hold_short_tiles_before_tall_ones(walker):
+    for case, got in zip(handover.CASES, replay(walker, handover.CASES)):
+        assert got["missing"] == 0 and got["requested_tall"] == 0, (case, got)
+        assert got["short_then_tall"] > 0, (case, got)
+
+
+def test_no_request_for_a_tall_item(walker):
+    rng = np.random.default_rng(0)
+    problems = []
+    for which, dtype, H, I in [("gateup", "bf16", 192, 8192), ("gateup", "fp8", 512, 4096), ("gateup", "fp8", 640, 4096),
+                               ("down", "bf16", 4096, 192), ("down", "fp8", 4096, 512), ("down", "fp8", 4160, 512)]:
+        for hot in (1537, 1825, 2161, 2405, 2900, 4096, 9000):
+            E = 8 if which == "gateup" and dtype == "bf16" else 32
+            # (256-row tiles: 113 rows an expert and more on average)
+            rows = [hot] + [int(v) for v in rng.integers(0, 400, E - 1)]
+            rows[1] += max(0, 150 * E - sum(rows))
+            problems.append((which, dtype, rows, H // 128 * 128 if dtype == "fp8" else H, I))
+    got = replay(walker, problems)
+    for case, g in zip(problems, got):
+        assert g["missing"] == 0 and g["requested_tall"] == 0, (case, g)
+    assert sum(g["short_then_tall"] for g in got) > 100 and sum(g["requested"] for g in got) > 0
