@@ -122,7 +122,8 @@ enum { MOE_WORK_RANGES = 8, MOE_SCHED_INTS = 16 };
  *   plan[0] tile rows (= moe_tile_rows)      plan[1] wavefronts per workgroup
  *   plan[2] 16-row weight blocks per wavefront   plan[3] output columns per workgroup
  *   plan[4] 1: XCD r works through work range r (whole tiles); 0: eight parts of equal item count
- *   plan[5] 1: a last round that fills at most half an XCD is handed out as half-width items
+ *   plan[5] 1: a last round that fills at most half of an XCD's compute units is handed out as half-width items
+ *           (with plan[4] = 1)
  *   plan[6] down projection inside moe_forward: 1, or 2 = K is cut in halves with items of their own
  *           (few experts with tall tiles and a long K, bf16): the halves' fp32 partial sums take the
  *           place of y in the workspace and the combine adds them, first half first, before it rounds a

@@ -170,9 +170,9 @@ struct Shape {
     }
     static_assert(DW >= DA && DA >= 1, "weights are copied at least as far ahead as token rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
-    // half-width items (see gemm_tile): wide workgroups of launches in whole ranges only (gemm_whole_ranges); the
-    // fp8 gate/up epilogue needs whole 128-column blocks
-    static constexpr bool HALF_ITEMS = NW >= 8 && !(FP8 && SWIGLU) && !SPLITK && MB_MAX >= 4;
+    // half-width items (see gemm_tile): wide workgroups; the fp8 gate/up epilogue needs whole 128-column blocks.
+    // Launches in whole ranges hand them out (see ItemWalk), whatever the height of their tiles.
+    static constexpr bool HALF_ITEMS = NW >= 8 && !(FP8 && SWIGLU) && !SPLITK;
     static_assert(!(FP8 && SWIGLU) || COLS == kQBlock, "fp8 gate/up: a workgroup re-quantises one 1x128 block per row");
 };
 
@@ -743,10 +743,13 @@ struct ItemWalk {
         // tallest tile of the list (its first record) has more than 128 rows.
         k.zigzag = !whole_ranges && (SH::SWIGLU || tiles[0].rows > 128);
         k.nchunks = ceil_div(k.items, col_tiles);
-        // A last round that would fill at most half of the XCD's workgroup slots is handed out as
-        // half-width items, two per column slab.
+        // A last round that would occupy at most half of the XCD's compute units is handed out as half-width
+        // items, two per column slab.  (Compute units, not workgroup slots: where two workgroups share a compute unit,
+        // which low tiles do, a round of 24 is the faster one whole.  Gate/up of 2048 x 1408 layers, halves against
+        // none: 40 and 48 experts 76 against 80 us (down, 4096 x 1536) and 91 against 98, rounds of 16 and 2; 64
+        // experts 113 against 110, a round of 24.)
         const int rest = k.items % round_slots;
-        k.halved = (SH::HALF_ITEMS && whole_ranges && rest > 0 && 2 * rest <= round_slots) ? rest : 0;
+        k.halved = (SH::HALF_ITEMS && whole_ranges && rest > 0 && 2 * rest <= GM_CUS / GM_XCDS) ? rest : 0;
         k.slots = k.zigzag ? k.nchunks * col_tiles : k.items + k.halved;
         return k;
     }

@@ -1,10 +1,11 @@
 // Walks the grouped GEMMs' schedules on the host, with the code that the kernels walk them with, and reports what follows
 // what in a workgroup (driven by tests/test_host_item_walk.py).
-//   stdin:  gateup|down bf16|fp8  K n_out max_tiles est_tiles  n  sched[0..15]  n records of eight ints
-//   stdout: items  missing  looped  short_then_tall  requested  requested_tall
+//   stdin:  gateup|down bf16|fp8  tile_rows (16, 32 or 256)  K n_out max_tiles est_tiles  n  sched[0..15]  n records of eight ints
+//   stdout: items  missing  looped  short_then_tall  requested  requested_tall  halves
 // items: (tile, column slab) items of the launch; missing: column-slab halves that are not handed out exactly once;
 // looped: items that follow another one in their workgroup; short_then_tall: of these, tall-loop items behind one of
-// gemm_tile; requested: items whose weights their predecessor requests; requested_tall: of these, tall-loop items.
+// gemm_tile; requested: items whose weights their predecessor requests; requested_tall: of these, tall-loop items; halves:
+// half-width items.
 #include <stdio.h>
 #include <string.h>
 
@@ -33,7 +34,7 @@ int walk(const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *s
     const LaunchPlan p = launch_plan<SH>(g, max_tiles, est_tiles);
     const int stride = p.blocks / MOE_WORK_RANGES;
     std::vector<int> seen((size_t)sched[0] * p.col_tiles * 2);
-    long looped = 0, short_tall = 0, requested = 0, requested_tall = 0;
+    long halves = 0, looped = 0, short_tall = 0, requested = 0, requested_tall = 0;
     for (int block = 0; block < p.blocks; ++block) {
         const ItemWalk w = ItemWalk::of_part<SH>(tiles.data(), sched, p.col_tiles, p.whole_ranges, p.round_slots, block % MOE_WORK_RANGES);
         Item cur{}, nxt{};
@@ -42,6 +43,7 @@ int walk(const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *s
         while (slot < w.slots) {
             const bool have_next = w.item_at(slot + stride, nxt);
             if (have) {
+                halves += cur.half != 0;
                 if (cur.half != 2) ++seen[(size_t)cur.work * 2];
                 if (cur.half != 1) ++seen[(size_t)cur.work * 2 + 1];
             }
@@ -60,8 +62,18 @@ int walk(const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *s
     }
     long missing = 0;
     for (int n : seen) missing += n != 1;
-    printf("%ld %ld %ld %ld %ld %ld\n", (long)seen.size() / 2, missing, looped, short_tall, requested, requested_tall);
+    printf("%ld %ld %ld %ld %ld %ld %ld\n", (long)seen.size() / 2, missing, looped, short_tall, requested, requested_tall, halves);
     return 0;
+}
+
+template <int MB>
+int walk_wide(bool swiglu, bool f8, const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *sched, int max_tiles,
+              int est_tiles)
+{
+    return swiglu ? (f8 ? walk<typename ShapesFor<MB, true, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
+                        : walk<typename ShapesFor<MB, true, false>::Wide>(g, tiles, sched, max_tiles, est_tiles))
+                  : (f8 ? walk<typename ShapesFor<MB, false, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
+                        : walk<typename ShapesFor<MB, false, false>::Wide>(g, tiles, sched, max_tiles, est_tiles));
 }
 
 }  // namespace
@@ -70,18 +82,17 @@ int main()
 {
     char which[16], dtype[16];
     GemmArgs g{};
-    int max_tiles, est_tiles, n;
-    while (scanf("%15s %15s %d %d %d %d %d", which, dtype, &g.K, &g.n_out, &max_tiles, &est_tiles, &n) == 7) {
+    int tile_rows, max_tiles, est_tiles, n;
+    while (scanf("%15s %15s %d %d %d %d %d %d", which, dtype, &tile_rows, &g.K, &g.n_out, &max_tiles, &est_tiles, &n) == 8) {
         int32_t sched[MOE_SCHED_INTS];
         for (int &v : sched) if (scanf("%d", &v) != 1) return 1;
         std::vector<moe_tile> tiles(n);
         for (moe_tile &t : tiles)
             for (int i = 0; i < 8; ++i) if (scanf("%d", (int *)&t + i) != 1) return 1;
         const bool swiglu = !strcmp(which, "gateup"), f8 = !strcmp(dtype, "fp8");
-        const int rc = swiglu ? (f8 ? walk<ShapesFor<16, true, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
-                                    : walk<ShapesFor<16, true, false>::Wide>(g, tiles, sched, max_tiles, est_tiles))
-                              : (f8 ? walk<ShapesFor<16, false, true>::Wide>(g, tiles, sched, max_tiles, est_tiles)
-                                    : walk<ShapesFor<16, false, false>::Wide>(g, tiles, sched, max_tiles, est_tiles));
+        const int rc = tile_rows == 256  ? walk_wide<16>(swiglu, f8, g, tiles, sched, max_tiles, est_tiles)
+                       : tile_rows == 32 ? walk_wide<2>(swiglu, f8, g, tiles, sched, max_tiles, est_tiles)
+                       : tile_rows == 16 ? walk_wide<1>(swiglu, f8, g, tiles, sched, max_tiles, est_tiles) : 1;
         if (rc) return rc;
     }
     return 0;

@@ -3,6 +3,7 @@ of low tiles with fewer K steps than stages and with many, 16- and 32-row tiles,
 import pytest
 import torch
 
+import test_gpu_tile_handover as handover
 from paper_2602_19128_amd import binding as moe
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +38,16 @@ def test_low_tiles_of_few_experts(rows, H, I):
         a, w = act[lo:hi].double(), w2[e].double().t()
         ref = a @ w
         assert ((y[lo:hi].double() - ref).abs() <= ref.abs() * 2.0 ** -8 + (a.abs() @ w.abs()) * 2.0 ** -20).all(), f"down, expert {e}"
+
+
+@pytest.mark.parametrize("which, dtype, rows, H, I", [
+    ("gateup", "bf16", [6] * 48, 256, 1408), ("gateup", "bf16", [3, 20] * 20, 192, 1664), ("down", "bf16", [16, 9] * 20, 4096, 192),
+    ("down", "fp8", [16, 15] * 20, 4096, 256), ("down", "fp8", [5] * 40, 4096, 128),
+])
+def test_half_width_items_of_low_tiles(which, dtype, rows, H, I):
+    """Wide workgroups of 16- and 32-row tiles whose last round is short (see test_last_round_of_low_tiles)."""
+    plan = moe.moe_gemm_plan(handover.config(which, dtype, rows, H, I), which)
+    assert plan["tile_rows"] <= 32 and plan["wavefronts"] == 8 and plan["whole_ranges"] and plan["half_items"]
+    items = len(rows) * -(-(I if which == "gateup" else H) // plan["columns"]) // 8
+    assert 1 <= items % 64 <= 16
+    handover.check_gemm(which, dtype, rows, H, I)

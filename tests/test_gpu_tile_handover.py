@@ -28,8 +28,8 @@ def _dequantise(q, scale, rows):
     return (q.double().view(N // rows, rows, K // 128, 128) * scale.double()[:, None, :, None]).view(N, K)
 
 
-@pytest.mark.parametrize("which, dtype, rows, H, I", CASES)
-def test_short_tile_then_tall_tile(which, dtype, rows, H, I):
+def check_gemm(which, dtype, rows, H, I):
+    """One grouped GEMM on shuffled tokens against float64, three times on the same inputs."""
     E, T, fp8 = len(rows), sum(rows), dtype == "fp8"
     cfg = config(which, dtype, rows, H, I)
     gen = torch.Generator("cuda").manual_seed(H + I)
@@ -70,3 +70,8 @@ def test_short_tile_then_tall_tile(which, dtype, rows, H, I):
             else:        # one bf16 rounding of fp32 sums
                 bound = ref.abs() * 2.0 ** -8 + mag.max() ** 2 * 2.0 ** -20
             assert ((gotd[lo:hi] - ref).abs() <= bound).all(), f"expert {e} of {hi - lo} rows"
+
+
+@pytest.mark.parametrize("which, dtype, rows, H, I", CASES)
+def test_short_tile_then_tall_tile(which, dtype, rows, H, I):
+    check_gemm(which, dtype, rows, H, I)

@@ -1,6 +1,6 @@
-"""The order in which workgroups of the 256-row launches take their items, replayed on the host with the kernels' own
-code (tests/gemm_items_main.cpp): every item is handed out once, and no item requests weights for a successor that a
-tall-tile loop computes, which lays out its LDS in another way."""
+"""The order in which workgroups take their items, replayed on the host with the kernels' own code
+(tests/gemm_items_main.cpp): every item is handed out once, no item requests weights for a successor that a tall-tile
+loop computes, which lays out its LDS in another way, and a short last round goes out as half-width items."""
 import os
 import subprocess
 
@@ -40,18 +40,18 @@ def schedule(rows, tile_rows):
     return [len(records)] + starts + [len(records)] + [0] * 6, records
 
 
-def replay(walker, problems):
+def replay(walker, problems, tile_rows=256):
     text = []
     for which, dtype, rows, H, I in problems:
         cfg = handover.config(which, dtype, rows, H, I)
         plan = moe.moe_gemm_plan(cfg, which)
-        assert (plan["tile_rows"], plan["wavefronts"], plan["blocks_per_wavefront"]) == (256, 8, 2)
-        sched, records = schedule(rows, 256)
+        assert (plan["tile_rows"], plan["wavefronts"], plan["blocks_per_wavefront"]) == (tile_rows, 8, 2)
+        sched, records = schedule(rows, tile_rows)
         K, n_out = (H, I) if which == "gateup" else (I, H)
-        text.append(" ".join(map(str, [which, dtype, K, n_out, moe.moe_max_tiles(cfg), min(sum(rows), len(rows)), len(records)]
+        text.append(" ".join(map(str, [which, dtype, tile_rows, K, n_out, moe.moe_max_tiles(cfg), min(sum(rows), len(rows)), len(records)]
                                  + sched + [v for r in records for v in r])))
     out = subprocess.run([walker], input="\n".join(text), capture_output=True, text=True, check=True).stdout.splitlines()
-    names = ("items", "missing", "looped", "short_then_tall", "requested", "requested_tall")
+    names = ("items", "missing", "looped", "short_then_tall", "requested", "requested_tall", "halves")
     return [dict(zip(names, map(int, line.split()))) for line in out]
 
 
@@ -76,3 +76,18 @@ def test_no_request_for_a_tall_item(walker):
     for case, g in zip(problems, got):
         assert g["missing"] == 0 and g["requested_tall"] == 0, (case, g)
     assert sum(g["short_then_tall"] for g in got) > 100 and sum(g["requested"] for g in got) > 0
+
+
+@pytest.mark.parametrize("which, rows, H, I, halves", [
+    ("gateup", [6] * 48, 2048, 1408, 8 * 2 * 2),                 # 66 items an XCD on 64 slots: two left over
+    ("gateup", [12] * 40, 1024, 1664, 8 * 2 * 1),                # 65 items
+    ("down", [16] * 40, 4096, 1536, 8 * 2 * 16),                 # 80 items: as many as half of the compute units
+    ("gateup", [6] * 64, 2048, 1408, 0),                         # 88 items: 24 left over, more than that
+    ("gateup", [12] * 64, 2048, 1408, 0),
+])
+def test_last_round_of_low_tiles(walker, which, rows, H, I, halves):
+    cfg = handover.config(which, "bf16", rows, H, I)
+    plan = moe.moe_gemm_plan(cfg, which)
+    assert plan["tile_rows"] <= 32 and plan["whole_ranges"] and plan["half_items"]
+    got, = replay(walker, [(which, "bf16", rows, H, I)], plan["tile_rows"])
+    assert got["missing"] == 0 and got["halves"] == halves
