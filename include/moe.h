@@ -148,7 +148,8 @@ MOE_API size_t moe_workspace_size(const moe_config *cfg);
  *   ids_out   [T,k] int32, experts in descending key order, equal keys -> lower index
  *   w_out     [T,k] fp32, w = s[id] (/ sum over the k if renormalize) * routed_scale
  *   workspace device scratch of at least moe_route_workspace_size(cfg) bytes
- * Non-finite inputs give unspecified but in-range ids.
+ * Infinite router weights and hidden states give the logits of an fp32 sum (infinite, or NaN where infinities meet);
+ * NaN keys give unspecified ids, in range and distinct.
  */
 MOE_API int moe_route(const moe_config *cfg, const void *x, const float *x_scale, const float *router_w,
               const float *bias, int32_t *ids_out, float *w_out,

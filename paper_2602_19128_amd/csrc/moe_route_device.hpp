@@ -251,7 +251,7 @@ __device__ __forceinline__ void route_token(const float (&z)[EPL], int lane, int
     for (int i = 0; i < EPL; ++i) {
         const int e = lane * EPL + i;
         const float c = s[i] + ((bias != nullptr && e < E) ? bias[e] : 0.f);
-        key[i] = (e < E) ? orderable(c) : 0u;
+        key[i] = (e < E) ? max(orderable(c), 1u) : 0u;     // (a NaN with all bits set is a candidate, too)
     }
 
     // ---- group limiting ----------------------------------------------------
@@ -320,17 +320,15 @@ __device__ __forceinline__ void route_token(const float (&z)[EPL], int lane, int
     }
 }
 
-// One wavefront per token: adds the partial logits of the H splits, then routes the token.
+// Adds a token's partial logits of the H splits; router_topk_token then routes it, one wavefront per token.
 // NB = splits whose partial logits are requested together (8, or 32 when H was cut into more than
 // 8 slices - few tokens, so registers are not what limits the kernel, the latency of one round of
 // loads after another is: 64 decode tokens 17 -> 9 us).
 template <int EPL, int NB>
-__device__ __forceinline__ void router_topk_token(const float *__restrict__ zpart, const float *__restrict__ bias,
-                                                  int32_t *__restrict__ ids, float *__restrict__ w,
-                                                  const TopkParams &p, int t, int lane)
+__device__ __forceinline__ void sum_partial_logits(const float *__restrict__ zpart, const TopkParams &p, int t, int lane,
+                                                   float (&z)[EPL])
 {
     const int E = p.E;
-    float z[EPL];
     // partial logits of the H splits, added in split order; the loads of NB splits are issued
     // together so that their latencies overlap
 #pragma unroll
@@ -374,7 +372,15 @@ __device__ __forceinline__ void router_topk_token(const float *__restrict__ zpar
 #pragma unroll
             for (int i = 0; i < EPL; ++i) z[i] += part[u][i];
     }
+}
 
+template <int EPL, int NB>
+__device__ __forceinline__ void router_topk_token(const float *__restrict__ zpart, const float *__restrict__ bias,
+                                                  int32_t *__restrict__ ids, float *__restrict__ w,
+                                                  const TopkParams &p, int t, int lane)
+{
+    float z[EPL];
+    sum_partial_logits<EPL, NB>(zpart, p, t, lane, z);
     route_token<EPL>(z, lane, t, bias, ids, w, p);
 }
 
