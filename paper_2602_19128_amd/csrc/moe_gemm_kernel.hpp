@@ -857,13 +857,9 @@ struct ShapesFor {
     static constexpr int DA = MB_MAX >= 16 ? 1 : 2;           // 16 row blocks: 32 KiB per token stage
     static constexpr int DW = 2;
     using Wide = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8>;
+    // (Four token and five weight stages in flight for launches of fewer workgroups than compute units are slower, at
+    // every length of K: down projection of one token, 2048 x 8192, 50 -> 58 us, of three Mixtral tokens 97 -> 102.)
     using Narrow = Shape<MB_MAX, 4, DA, 3, SWIGLU, FP8>;
-    // Low tiles with a long K, in a launch of fewer workgroups than compute units: the copies of a step are waited for in
-    // the order they were issued, so what is in flight is DA + 1 stages whatever DW says, and one workgroup per compute
-    // unit (three Mixtral tokens: 192) streamed at 5.7 TB/s with 32 KiB each; with 64 KiB 6.6 (down projection 124 ->
-    // 107 us).  Where two of the small workgroups share a compute unit they are the faster ones: 40 32-row tiles of
-    // 2560 x 1408, 163 us a layer against 181 with the deep rings, which fill the LDS with one.
-    using NarrowDeep = Shape<MB_MAX, 4, MB_MAX <= 2 ? 4 : DA, MB_MAX <= 2 ? 5 : 3, SWIGLU, FP8>;
     using Wide4 = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8, SWIGLU ? 2 : 4>;
     using WideSplit = Shape<MB_MAX, 8, DA, DW, false, false, 2, true>;
 };
@@ -884,10 +880,6 @@ int launch_for_rows(const GemmArgs &g, const moe_tile *tiles, const int32_t *sch
             return launch_shape<typename SF::Wide4>(g, tiles, sched, max_tiles, est_tiles, s);
         return MOE_ERR_UNSUPPORTED;
     case GEMM_NARROW:
-        if constexpr (!(FP8 && SWIGLU) && MB_MAX <= 2)
-            if (g.K * (FP8 ? 1 : 2) / GM_STEP_BYTES >= kLongK &&
-                (long)est_tiles * ceil_div(g.n_out, SF::NarrowDeep::COLS) <= kComputeUnits)
-                return launch_shape<typename SF::NarrowDeep>(g, tiles, sched, max_tiles, est_tiles, s);
         if constexpr (!(FP8 && SWIGLU))
             return launch_shape<typename SF::Narrow>(g, tiles, sched, max_tiles, est_tiles, s);
         return MOE_ERR_UNSUPPORTED;

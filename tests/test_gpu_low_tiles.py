@@ -1,5 +1,5 @@
-"""Grouped GEMMs of a handful of tokens on few, wide experts: fewer tiles than XCDs in equal parts, the deep copy rings
-of low tiles with fewer K steps than stages and with many, 16- and 32-row tiles, experts without a row."""
+"""Grouped GEMMs of a handful of tokens on few, wide experts: fewer tiles than XCDs in equal parts, fewer K steps than
+copy stages and many, 16- and 32-row tiles, experts without a row, half-width items."""
 import pytest
 import torch
 
