@@ -112,9 +112,9 @@ typedef struct moe_tile {
  * Experts are ranked by their row count, largest first (equal counts: lower index
  * first), and dealt to the ranges in snake order (0..7, 7..0, ...), so every range
  * lists its tallest tiles first and the ranges carry similar loads.  The grouped
- * GEMMs give range r to XCD r when a range is a few tall tiles, and otherwise cut the
- * list into eight parts of equal tile-slab count (the ranges, up to a tile or two
- * at their ends). */
+ * GEMMs give range r to XCD r when a range is a few tiles (and not a few low ones
+ * with a long K), and otherwise cut the list into eight parts of equal tile-slab count
+ * (the ranges, up to a tile or two at their ends); moe_gemm_plan tells which. */
 enum { MOE_WORK_RANGES = 8, MOE_SCHED_INTS = 16 };
 
 /* Launch shape of a grouped GEMM for this problem (a property of the problem statement alone;

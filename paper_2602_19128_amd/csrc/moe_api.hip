@@ -142,7 +142,8 @@ int moe_gemm_plan(const moe_config *cfg, int which, int32_t *plan)
     plan[1] = waves;
     plan[2] = blocks;
     plan[3] = waves * (swiglu ? 16 : 16 * blocks);
-    plan[4] = gemm_whole_ranges(rows / 16, (swiglu ? cfg->H : cfg->I) * (f8 ? 1 : 2) / GM_STEP_BYTES, est) ? 1 : 0;
+    const int col_tiles = ceil_div(swiglu ? cfg->I : cfg->H, plan[3]) * ks;
+    plan[4] = gemm_order(rows / 16, (swiglu ? cfg->H : cfg->I) * (f8 ? 1 : 2) / GM_STEP_BYTES, est, col_tiles) == ORDER_RANGES;
     plan[5] = (waves >= 8 && !(f8 && swiglu) && ks == 1) ? 1 : 0;
     plan[6] = ks;
     return MOE_OK;

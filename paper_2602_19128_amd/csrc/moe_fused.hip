@@ -75,7 +75,7 @@ struct FusedArgs {
     int32_t *sched;
     // expert GEMMs
     GemmArgs g1, g2;
-    int col_tiles1, col_tiles2, whole_ranges;
+    int col_tiles1, col_tiles2, order1, order2;
     // combine
     uint16_t *out;
     int T, out_H, top_k;
@@ -221,9 +221,9 @@ __global__ __launch_bounds__(FZ_THREADS) void fused_forward_kernel(FusedArgs a)
         // ---- expert GEMMs and combine --------------------------------------------------------------
         using SH1 = typename ShapesFor<MB_MAX, true, false>::Narrow;
         using SH2 = typename ShapesFor<MB_MAX, false, false>::Narrow;
-        gemm_items<SH1>(a.g1, a.tiles, a.sched, a.col_tiles1, a.whole_ranges, 32, block, nblocks, smem);
+        gemm_items<SH1>(a.g1, a.tiles, a.sched, a.col_tiles1, a.order1, 32, block, nblocks, smem);
         sync.meet(bar, false), ++bar;                         // act is complete
-        gemm_items<SH2>(a.g2, a.tiles, a.sched, a.col_tiles2, a.whole_ranges, 32, block, nblocks, smem);
+        gemm_items<SH2>(a.g2, a.tiles, a.sched, a.col_tiles2, a.order2, 32, block, nblocks, smem);
         sync.meet(bar, false), ++bar;                         // y is complete
         const long long shares = (long long)a.T * (a.out_H / 8);
         for (long long idx = (long long)block * FZ_THREADS + threadIdx.x; idx < shares; idx += (long long)nblocks * FZ_THREADS)
@@ -320,11 +320,12 @@ int launch_fused(const moe_config &c, int tile_rows, int max_tiles, const void *
                               ? (int)sizeof(LogitsLds) : (int)(sizeof(int) * permute_lds_ints(FZ_THREADS, a.EL));
     a.g1 = gateup_args(c, x, nullptr, w1, nullptr, sorted_pair, act, nullptr);
     a.g2 = down_args(c, act, nullptr, w2, nullptr, y, 1);   // (tiles of at most 64 rows: K is never split here)
-    a.whole_ranges = expected_tiles(c) <= 8 * MOE_WORK_RANGES ? 1 : 0;
     const int mb = tile_rows / 16;
     const int cols1 = 16 * 4, cols2 = 32 * 4;                 // columns per narrow workgroup (gate/up, down)
     a.col_tiles1 = ceil_div(c.I, cols1);
     a.col_tiles2 = ceil_div(c.H, cols2);
+    a.order1 = gemm_order(mb, c.H * 2 / GM_STEP_BYTES, expected_tiles(c), a.col_tiles1);
+    a.order2 = gemm_order(mb, c.I * 2 / GM_STEP_BYTES, expected_tiles(c), a.col_tiles2);
     long need = route_blocks;
     const long items1 = (long)max_tiles * a.col_tiles1, items2 = (long)max_tiles * a.col_tiles2;
     if (items1 > need) need = items1;

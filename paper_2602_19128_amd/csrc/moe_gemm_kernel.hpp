@@ -696,13 +696,13 @@ __device__ __forceinline__ bool dispatch_blocks(int nb, const GemmArgs &g, const
 // workgroups with blockIdx % 8 == r, which share an L2) works through part r of the resulting item
 // sequence (tile-major, one item per column slab), so the workgroups running side by side there
 // are on neighbouring column slabs of the same expert tile and share its token rows through that L2.
-//   whole_ranges = 1: part r is work range r, whole tiles only.  With few tiles per XCD this
+//   ORDER_RANGES: part r is work range r, whole tiles only.  With few tiles per XCD this
 //     keeps each XCD on as few tiles at a time as possible (their token rows compete with the
 //     weight stream for its L2; measured +20 % on a 32-expert share when parts cut through tiles).
-//     Not for low tiles, see gemm_whole_ranges.
-//   whole_ranges = 0: the sequence is cut into eight equal parts, which coincide with the ranges
-//     up to a tile or two at their ends.  Every tile streams the same weight bytes, so with many
-//     tiles per XCD equal item counts are what lets the XCDs finish together.
+//   ORDER_PARTS, ORDER_PARTS_IN_TURN: the sequence is cut into eight equal parts, which coincide
+//     with the ranges up to a tile or two at their ends.  Every tile streams the same weight bytes,
+//     so with many tiles per XCD equal item counts are what lets the XCDs finish together.
+// gemm_order chooses.
 // The launch normally has one workgroup per item; the loop only matters when a part holds more
 // work than its share of the grid.
 // Workgroup `block` of `nblocks` (a multiple of MOE_WORK_RANGES) works through its share of the
@@ -720,12 +720,12 @@ struct ItemWalk {
 
     template <class SH>
     __host__ __device__ __forceinline__ static ItemWalk of_part(const moe_tile *tiles, const int32_t *sched, int col_tiles,
-                                                                int whole_ranges, int round_slots, int part)
+                                                                int order, int round_slots, int part)
     {
         ItemWalk k{};
         k.tiles = tiles;
         k.col_tiles = col_tiles;
-        if (whole_ranges) {
+        if (order == ORDER_RANGES) {
             k.first = sched[1 + part] * col_tiles;
             k.items = sched[2 + part] * col_tiles - k.first;
         } else {
@@ -741,7 +741,7 @@ struct ItemWalk {
         // prefills; the down GEMM -12 % when the tallest tiles are full height (hot experts), but +5 % when
         // every tile is low, where tallest-first only shortens the tail - so it alternates only when the
         // tallest tile of the list (its first record) has more than 128 rows.
-        k.zigzag = !whole_ranges && (SH::SWIGLU || tiles[0].rows > 128);
+        k.zigzag = order == ORDER_PARTS && (SH::SWIGLU || tiles[0].rows > 128);
         k.nchunks = ceil_div(k.items, col_tiles);
         // A last round that would occupy at most half of the XCD's compute units is handed out as half-width
         // items, two per column slab.  (Compute units, not workgroup slots: where two workgroups share a compute unit,
@@ -749,7 +749,7 @@ struct ItemWalk {
         // none: 40 and 48 experts 76 against 80 us (down, 4096 x 1536) and 91 against 98, rounds of 16 and 2; 64
         // experts 113 against 110, a round of 24.)
         const int rest = k.items % round_slots;
-        k.halved = (SH::HALF_ITEMS && whole_ranges && rest > 0 && 2 * rest <= GM_CUS / GM_XCDS) ? rest : 0;
+        k.halved = (SH::HALF_ITEMS && order == ORDER_RANGES && rest > 0 && 2 * rest <= GM_CUS / GM_XCDS) ? rest : 0;
         k.slots = k.zigzag ? k.nchunks * col_tiles : k.items + k.halved;
         return k;
     }
@@ -785,10 +785,10 @@ struct ItemWalk {
 // its token rows through L2; a workgroup that took consecutive slots instead measured +10..15 %).
 template <class SH>
 __device__ __forceinline__ void gemm_items(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched,
-                                           int col_tiles, int whole_ranges, int round_slots, int block,
+                                           int col_tiles, int order, int round_slots, int block,
                                            int nblocks, unsigned char *smem)
 {
-    const ItemWalk walk = ItemWalk::of_part<SH>(tiles, sched, col_tiles, whole_ranges, round_slots, block % MOE_WORK_RANGES);
+    const ItemWalk walk = ItemWalk::of_part<SH>(tiles, sched, col_tiles, order, round_slots, block % MOE_WORK_RANGES);
     const int stride = nblocks / MOE_WORK_RANGES;
     Item cur{}, nxt{};
     int slot = block / MOE_WORK_RANGES;
@@ -811,14 +811,14 @@ __device__ __forceinline__ void gemm_items(const GemmArgs &g, const moe_tile *ti
 template <class SH>
 __global__ __launch_bounds__(SH::THREADS) void grouped_gemm_kernel(GemmArgs g, const moe_tile *__restrict__ tiles,
                                                                    const int32_t *__restrict__ sched, int col_tiles,
-                                                                   int whole_ranges, int round_slots)
+                                                                   int order, int round_slots)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    gemm_items<SH>(g, tiles, sched, col_tiles, whole_ranges, round_slots, (int)blockIdx.x, (int)gridDim.x, smem);
+    gemm_items<SH>(g, tiles, sched, col_tiles, order, round_slots, (int)blockIdx.x, (int)gridDim.x, smem);
 }
 
 // Grid and item walk of a launch.
-struct LaunchPlan { int col_tiles, round_slots, blocks, whole_ranges; };
+struct LaunchPlan { int col_tiles, round_slots, blocks, order; };
 
 template <class SH>
 LaunchPlan launch_plan(const GemmArgs &g, int max_tiles, int est_tiles)
@@ -833,7 +833,7 @@ LaunchPlan launch_plan(const GemmArgs &g, int max_tiles, int est_tiles)
     // of a last round) keeps the loop in the kernel at one trip, unless hot experts make a range longer than that
     const int part_slots = (ceil_div(max_tiles, GM_XCDS) + 1) * p.col_tiles + (SH::HALF_ITEMS ? p.round_slots / 2 : 0);
     p.blocks = part_slots * GM_XCDS;
-    p.whole_ranges = gemm_whole_ranges(SH::MB_MAX, g.K * (SH::FP8 ? 1 : 2) / GM_STEP_BYTES, est_tiles) ? 1 : 0;
+    p.order = gemm_order(SH::MB_MAX, g.K * (SH::FP8 ? 1 : 2) / GM_STEP_BYTES, est_tiles, p.col_tiles);
     return p;
 }
 
@@ -847,7 +847,7 @@ int launch_shape(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched,
     const int rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), SH::LDS_BYTES);
     if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL(kern, dim3(p.blocks), dim3(SH::THREADS), SH::LDS_BYTES, s, g, tiles, sched, p.col_tiles,
-                       p.whole_ranges, p.round_slots);
+                       p.order, p.round_slots);
     return check_launch();
 }
 

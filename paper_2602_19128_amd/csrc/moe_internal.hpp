@@ -156,18 +156,31 @@ inline int expected_tiles(const moe_config &c)
 }
 
 // K steps from which a workgroup's stream, and not its start, is its time: low tiles choose their launch by it
-// (16 tokens of 256 x 128 experts, 4 and 2 steps: 22.1 us a layer with the simple launch, 23.1 with the other).
+// (16 tokens of 256 x 128 experts, 4 and 2 steps: 22.1 us a layer with the simple launch, 23.1 with the other;
+// 8 and 24 experts of 256 to 1024 columns, 4 to 16 steps: the same within 0.3 us either way).
 constexpr int kLongK = 16;
 
-// Whether XCD r works through work range r, whole tiles only, or through one of eight equal parts of the items
-// (see gemm_items): whole ranges when an XCD has at most eight tiles, unless they are low and at most four.  Token rows
-// of low tiles are too few to matter to an L2, while ranges of a few whole tiles leave XCDs idle: three Mixtral tokens
-// hit six experts, six ranges (gate/up 269 -> 205 us with equal parts); fp8 share of 26 32-row tiles, three or four a
-// range, down 66 -> 59 us.  With 60 32-row tiles equal parts were 3 % slower, with 60 64-row tiles 15 % (39 -> 45 us).
-inline bool gemm_whole_ranges(int mb_max, int k_steps, int est_tiles)
+// How the XCDs share a launch's items (see ItemWalk).
+//   ranges         XCD r takes work range r, whole tiles only: where an XCD has at most eight tiles.
+//   parts          eight equal parts, each from both of its ends: more tiles than that.
+//   parts in turn  eight equal parts, each from its start: launches of at most four low tiles an XCD whose K is long and
+//                  whose ranges hold more items than half of an XCD's compute units.  Token rows of low tiles are too few
+//                  to matter to an L2, while ranges of a few whole tiles leave XCDs idle.  Ranges / parts in turn, us:
+//                  three Mixtral tokens (five or six experts hit), gate/up 249 / 197, down 122 / 97; 20 experts of
+//                  2048 x 1408, 120 tokens, gate/up 50 / 38; 24 of 7168 x 2048, 12 tokens, down 88 / 75; fp8 share of
+//                  32 experts, 64 tokens, down 64 / 60.  Low tiles are alike, so nothing is gained by mixing them from
+//                  both ends, and 28 and 32 experts lose by it: gate/up of 168 tokens, 2048 x 1408, 55 / 55 and 60 from
+//                  both ends, 64 tokens of 4096 x 1536 119 / 118 and 127.  Ranges of at most 16 items have a compute unit
+//                  each wherever they are: one token, 2048 x 8192, down 49 / 50.5.  60 tiles are slower in parts: of 32
+//                  rows 3 %, of 64 rows 15 % (39 / 45).
+enum GemmOrder { ORDER_PARTS = 0, ORDER_RANGES = 1, ORDER_PARTS_IN_TURN = 2 };
+inline GemmOrder gemm_order(int mb_max, int k_steps, int est_tiles, int col_tiles)
 {
-    const bool few_low = mb_max <= 2 && est_tiles <= 4 * MOE_WORK_RANGES && k_steps >= kLongK;
-    return est_tiles <= 8 * MOE_WORK_RANGES && !few_low;
+    const int range_items = ceil_div(est_tiles, MOE_WORK_RANGES) * col_tiles;
+    if (mb_max <= 2 && est_tiles <= 4 * MOE_WORK_RANGES && k_steps >= kLongK &&
+        range_items > kComputeUnits / MOE_WORK_RANGES / 2)
+        return ORDER_PARTS_IN_TURN;
+    return est_tiles <= 8 * MOE_WORK_RANGES ? ORDER_RANGES : ORDER_PARTS;
 }
 
 // Tile height: the smallest of 16..256 that holds an expert's rows with a binomial safety

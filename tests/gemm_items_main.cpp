@@ -36,7 +36,7 @@ int walk(const GemmArgs &g, const std::vector<moe_tile> &tiles, const int32_t *s
     std::vector<int> seen((size_t)sched[0] * p.col_tiles * 2);
     long halves = 0, looped = 0, short_tall = 0, requested = 0, requested_tall = 0;
     for (int block = 0; block < p.blocks; ++block) {
-        const ItemWalk w = ItemWalk::of_part<SH>(tiles.data(), sched, p.col_tiles, p.whole_ranges, p.round_slots, block % MOE_WORK_RANGES);
+        const ItemWalk w = ItemWalk::of_part<SH>(tiles.data(), sched, p.col_tiles, p.order, p.round_slots, block % MOE_WORK_RANGES);
         Item cur{}, nxt{};
         int slot = block / MOE_WORK_RANGES;
         bool have = w.item_at(slot, cur);

@@ -9,15 +9,18 @@ from paper_2602_19128_amd import binding as moe
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows, H, I", [
-    ([1], 64, 64), ([2, 0, 1, 0, 0, 3], 128, 320), ([1, 1, 0, 1, 1, 1, 1], 1024, 4160), ([16, 15, 1], 576, 2048),
-    ([17, 32, 1, 9], 448, 1024), ([12] * 40, 256, 192), ([3, 1, 2], 1088, 256),
+# parts: down launches in equal parts, which the rule keeps to ranges of more than 16 column slabs
+@pytest.mark.parametrize("rows, H, I, parts", [
+    ([1], 64, 64, False), ([2, 0, 1, 0, 0, 3], 128, 320, False), ([1, 1, 0, 1, 1, 1, 1], 1024, 4160, False),
+    ([16, 15, 1], 576, 2048, False), ([17, 32, 1, 9], 448, 1024, False), ([12] * 40, 256, 192, False), ([3, 1, 2], 1088, 256, False),
+    ([1, 1, 0, 1, 1, 1, 1], 2176, 4160, True), ([16, 15, 1], 2112, 2048, True), ([17, 32, 1, 9], 4096, 1024, True),
+    ([5] * 18, 768, 1088, True), ([20, 0, 1] * 10, 640, 1024, True), ([9] * 33, 640, 1024, False), ([1, 1, 0, 1, 1, 1, 1], 2048, 4160, False),
 ])
-def test_low_tiles_of_few_experts(rows, H, I):
+def test_low_tiles_of_few_experts(rows, H, I, parts):
     E, T = len(rows), sum(rows)
     cfg = moe.MoEConfig(T, H, I, E, 1, 0, 1, 1, 1, 1, 0, 1.0, 0, 0, 0)
     plan = moe.moe_gemm_plan(cfg, "down")
-    assert plan["tile_rows"] <= 32 and plan["wavefronts"] == 4 and plan["whole_ranges"] == (I < 1024)
+    assert plan["tile_rows"] <= 32 and plan["wavefronts"] == 4 and plan["whole_ranges"] == (not parts)
     gen = torch.Generator("cuda").manual_seed(H + I)
     ids = torch.repeat_interleave(torch.arange(E), torch.tensor(rows)).cuda()[torch.randperm(T, generator=gen, device="cuda")]
     ids = ids.to(torch.int32).view(T, 1)

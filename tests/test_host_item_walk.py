@@ -91,3 +91,14 @@ def test_last_round_of_low_tiles(walker, which, rows, H, I, halves):
     assert plan["tile_rows"] <= 32 and plan["whole_ranges"] and plan["half_items"]
     got, = replay(walker, [(which, "bf16", rows, H, I)], plan["tile_rows"])
     assert got["missing"] == 0 and got["halves"] == halves
+
+
+@pytest.mark.parametrize("which, rows, H, I", [
+    ("gateup", [2, 0, 1, 5] * 8, 1024, 2048), ("gateup", [1, 3] * 4, 2048, 8192), ("down", [12, 7] * 16, 4096, 1024),
+])
+def test_parts_in_turn(walker, which, rows, H, I):
+    """A few low tiles with a long K: eight equal parts."""
+    plan = moe.moe_gemm_plan(handover.config(which, "bf16", rows, H, I), which)
+    assert plan["tile_rows"] <= 32 and not plan["whole_ranges"]
+    got, = replay(walker, [(which, "bf16", rows, H, I)], plan["tile_rows"])
+    assert got["missing"] == 0 and got["halves"] == 0 and got["looped"] == 0
