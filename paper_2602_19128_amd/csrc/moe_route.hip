@@ -46,6 +46,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 rt_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float rt_f32x4;
 
 constexpr int RM_MANY_TOKENS = 512;        // from here on the tall workgroups, see mfma_grid
+constexpr size_t RM_FEW_PARTIALS = 512 << 10;   // partial logits (2 MB) that cost less than the round trips they save, see mfma_grid
 constexpr int RM_BK = 32;                  // hidden elements per K step (one MFMA deep)
 
 typedef __attribute__((ext_vector_type(2))) float rt_f32x2;
@@ -371,7 +372,17 @@ MfmaGrid mfma_grid(const moe_config &c)
     if (want > chunks) want = chunks;
     if (want < 1) want = 1;
     int per = ceil_div(chunks, want) * RM_BK;
-    if (c.dtype == MOE_DTYPE_FP8_E4M3) per = ceil_div(per, kQBlock) * kQBlock;   // splits end on scale-block edges
+    if (c.dtype == MOE_DTYPE_FP8_E4M3) {
+        // fp8 slices are whole scale blocks, unless few tokens make the call a chain of round trips (a slice that ends inside
+        // a block folds its part in with the same scale): then all the slices there are, or at least eight, while the
+        // partial logits they leave are few.  Whole blocks / this, us: 100 tokens of 32 experts, H = 512, 8.7 / 7.5; 16 of
+        // 64, H = 1024, 7.8 / 6.6; 300 of 256, H = 512, 10.2 / 9.6.  Beyond, the top-k kernel pays for them: 200 of 256,
+        // H = 1024, 10.5 and with slices of 32 12.0; 64 of 512, H = 512, 10.8 and 12.9; 511 of 512, H = 256, 11.4 and 12.2.
+        auto partials = [&](int p) { return (size_t)ceil_div(c.H, p) * c.T * c.E; };
+        const int whole = ceil_div(per, kQBlock) * kQBlock, eighth = max(per, ceil_div(chunks, 8) * RM_BK);
+        if (!g.few || c.E > 256 || partials(per) >= RM_FEW_PARTIALS)
+            per = g.few && eighth < whole && partials(eighth) <= 2 * RM_FEW_PARTIALS ? eighth : whole;
+    }
     g.k_per_split = per;
     g.splits = ceil_div(c.H, per);
     return g;

@@ -17,6 +17,8 @@ CASES = [
     syn.Workload("below_a_tile", T=63, H=384, I=128, E=130, top_k=6, fp8=True),
     syn.Workload("above_a_tile", T=65, H=640, I=128, E=256, top_k=8, n_group=8, topk_group=4, fp8=True, **GROUPED),
     syn.Workload("quantised_here", T=70, H=256, I=128, E=64, top_k=6, n_group=4, topk_group=2, fp8=True, quantize_x=True, **GROUPED),
+    syn.Workload("eight_slices", T=201, H=512, I=128, E=256, top_k=8, fp8=True),          # slices of half a scale block
+    syn.Workload("whole_blocks", T=511, H=384, I=128, E=384, top_k=4, fp8=True),
     syn.Workload("bf16_ragged", T=200, H=1344, I=64, E=49, top_k=6),
     syn.Workload("bf16_most", T=511, H=192, I=64, E=512, top_k=8),
 ]
