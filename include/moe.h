@@ -130,6 +130,8 @@ enum { MOE_WORK_RANGES = 8, MOE_SCHED_INTS = 16 };
  *           row to bf16.  moe_grouped_gemm_down itself always reduces over the whole of K (plan[1..5]
  *           with which = 1 describe what moe_forward launches), so for such a problem the two differ in
  *           the order of the fp32 sum, both inside the stated tolerance.
+ *   plan[7] row blocks (of 16) from which a tile goes through the loop for tall tiles, 0: none does.  bf16: tiles
+ *           of experts with three tiles and more; fp8: unless the token scales are off the 16-byte grid
  * Returns MOE_OK or the error code of the problem statement. */
 enum { MOE_GEMM_PLAN_INTS = 8 };
 MOE_API int moe_gemm_plan(const moe_config *cfg, int which, int32_t *plan /* HOST, MOE_GEMM_PLAN_INTS */);

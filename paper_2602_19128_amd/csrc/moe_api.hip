@@ -146,6 +146,8 @@ int moe_gemm_plan(const moe_config *cfg, int which, int32_t *plan)
     plan[4] = gemm_order(rows / 16, (swiglu ? cfg->H : cfg->I) * (f8 ? 1 : 2) / GM_STEP_BYTES, est, col_tiles) == ORDER_RANGES;
     plan[5] = (waves >= 8 && !(f8 && swiglu) && ks == 1) ? 1 : 0;
     plan[6] = ks;
+    if (rows >= 256 && wd == GEMM_WIDE)
+        plan[7] = !f8 ? kTallBlocksBf16 : (swiglu ? cfg->H : cfg->I) % (kTallStepsFp8 * GM_STEP_BYTES) == 0 ? kTallBlocksFp8 : 0;
     return MOE_OK;
 }
 

@@ -157,10 +157,9 @@ struct Shape {
     // one fp32 activation scale per token row, copied 64 rows (one wavefront) at a time
     static constexpr int SC_STAGE_BYTES = FP8 ? ((MB_MAX * 16 + 63) / 64) * 256 : 0;
     static constexpr int RING_BYTES = A_RING_BYTES + W_RING_BYTES + (DA + 1) * SC_STAGE_BYTES;
-    // Tall tiles (moe_gemm_tall.hpp).  fp8: TALL_MIN row blocks and more take gemm_tile_tall8, whose wavefronts want
-    // four row blocks each.  bf16: nine row blocks and more of an expert with TALL_COUNT tiles take gemm_tile_tall16.
+    // launches with a tall-tile loop (see takes_tall_loop), and the row blocks it starts at
     static constexpr bool TALL = MB_MAX >= 16 && NW == 8 && BPW == 2;
-    static constexpr int TALL_MIN = FP8 ? 8 : 9, TALL_COUNT = 3;
+    static constexpr int TALL_MIN = FP8 ? kTallBlocksFp8 : kTallBlocksBf16;
     static constexpr int TALL_BYTES = !TALL ? 0 : FP8 ? 4 * 256 * 128 + 3 * 256 * 16 : 5 * 256 * 128;
     static constexpr int LDS_BYTES = RING_BYTES > TALL_BYTES ? RING_BYTES : TALL_BYTES;
     // LDS of gemm_tile's staged output tile of nb row blocks (it lies over the token ring, from its start)
@@ -192,8 +191,8 @@ __host__ __device__ __forceinline__ bool takes_tall_loop(const GemmArgs &g, cons
     } else {
         if (item.half || ceil_div(item.tile.rows, 16) < SH::TALL_MIN) return false;
         // fp8: K in whole blocks of four steps, whose scales are copied 16 bytes at a time
-        if constexpr (SH::FP8) return g.K % (4 * GM_STEP_BYTES) == 0 && ((uintptr_t)g.a_scale & 15) == 0;
-        else return item.tile.count >= SH::TALL_COUNT;
+        if constexpr (SH::FP8) return g.K % (kTallStepsFp8 * GM_STEP_BYTES) == 0 && ((uintptr_t)g.a_scale & 15) == 0;
+        else return item.tile.count >= kTallCountBf16;
     }
 }
 

@@ -155,10 +155,19 @@ inline int expected_tiles(const moe_config &c)
     return (int)(pairs < el ? pairs : el);
 }
 
-// K steps from which a workgroup's stream, and not its start, is its time: low tiles choose their launch by it
-// (16 tokens of 256 x 128 experts, 4 and 2 steps: 22.1 us a layer with the simple launch, 23.1 with the other;
-// 8 and 24 experts of 256 to 1024 columns, 4 to 16 steps: the same within 0.3 us either way).
+// K steps from which low tiles may go to the XCDs in parts.  Drawn when every such launch did (16 tokens of 256 x 128
+// experts, 4 and 2 steps: 22.1 us a layer in ranges, 23.1 in parts); with ranges of few items kept apart, as now, shorter K
+// is no slower in parts either (three tokens, 8 experts, H = 512, I = 4096, gate/up 11.9 / 8.7; 24 experts, H = 256, 17.7 / 17.4).
 constexpr int kLongK = 16;
+
+// The tall-tile loops (moe_gemm_tall.hpp), of the wide launches of 256-row tiles.  fp8: tiles of this many row blocks and
+// more (its wavefronts want four each; from 9 or 12 on, gate/up of 16384 tokens on the 32-expert share
+// takes 512 or 525 us instead of 510) where K is
+// whole blocks of four steps.  bf16: this many row blocks and more of experts with three tiles and more; gate/up of eight
+// 4096 x 14336 experts with 600 rows each 1070 -> 1009 us, with 900 rows 1546 -> 1461.  With two tiles some gain (300 rows
+// 622 -> 567) and the DeepSeek-shaped prefill, whose weight stream is the time, loses 2 %.
+constexpr int kTallBlocksFp8 = 8, kTallBlocksBf16 = 9, kTallCountBf16 = 3;
+constexpr int kTallStepsFp8 = 4;
 
 // How the XCDs share a launch's items (see ItemWalk).
 //   ranges         XCD r takes work range r, whole tiles only: where an XCD has at most eight tiles.

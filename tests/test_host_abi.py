@@ -174,6 +174,32 @@ def test_parity_cases_reach_the_kernel_shapes_the_benchmarks_run(lib):
     assert lib.moe_gemm_plan(C.byref(moe.MoEConfig.from_workload(W["tiny"])), 2, (C.c_int32 * 8)()) == -1
 
 
+def test_tall_tile_cases_reach_the_loops_the_benchmarks_run(lib):
+    """Which launches have a tall-tile loop, for the benchmark workloads and for the cases of the tall-tile tests."""
+    import test_gpu_tall_tiles as tt
+    import test_gpu_tile_handover as th
+    plan = lambda wl, which: moe.moe_gemm_plan(moe.MoEConfig.from_workload(wl), which)["tall_from"]
+    W = syn.WORKLOADS
+    for name in ("mixtral_prefill", "dsv3_prefill", "dsv3_prefill_skew"):
+        assert plan(W[name], "gateup") == 9 and plan(W[name], "down") == 9
+    for name in ("fp8_local32", "fp8_local32_qx"):
+        assert plan(W[name], "gateup") == 8 and plan(W[name], "down") == 8
+    for name in ("tiny", "dsv3_decode", "fp8_prefill"):
+        assert plan(W[name], "gateup") == 0 and plan(W[name], "down") == 0
+    cases = lambda test: next(m for m in test.pytestmark if m.name == "parametrize").args[1]
+    for rows, H, I, down_wide in cases(tt.test_tall_fp8_tiles):
+        cfg = th.config("gateup", "fp8", rows, H, I)
+        assert moe.moe_gemm_plan(cfg, "gateup")["tall_from"] == (0 if H % 512 else 8)
+        assert moe.moe_gemm_plan(cfg, "down")["tall_from"] == (8 if down_wide else 0)
+    for H, I in cases(tt.test_tall_bf16_tiles):
+        cfg = th.config("gateup", "bf16", [1825, 1024, 700, 600, 513, 257, 40, 0], H, I)
+        assert moe.moe_gemm_plan(cfg, "gateup" if I > H else "down")["tall_from"] == 9
+    for which, dtype, rows, H, I in th.CASES:
+        assert moe.moe_gemm_plan(th.config(which, dtype, rows, H, I), which)["tall_from"] == (8 if dtype == "fp8" else 9)
+    # K that is no whole number of blocks of four steps
+    assert moe.moe_gemm_plan(th.config("gateup", "fp8", [300] * 32, 640, 4096), "gateup")["tall_from"] == 0
+
+
 def test_single_launch_path_is_a_property_of_the_problem_statement(lib):
     """Which problems moe_forward runs as one launch once that is switched on (host logic only; the
     GPU tests compare the paths)."""
