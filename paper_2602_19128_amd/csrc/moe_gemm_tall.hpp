@@ -1,5 +1,5 @@
-// Tall tiles (more than seven 16-row blocks) of the fp8 expert GEMMs; included by moe_gemm_kernel.hpp, which
-// describes what both kinds of tiles share.
+// K loops for tall tiles of the expert GEMMs (which tiles: takes_tall_loop); included by moe_gemm_kernel.hpp, which
+// describes what all tiles share.  First the fp8 loop; what the bf16 loop does otherwise stands before it.
 //
 // In gemm_tile every wavefront reads all token rows of a K step from LDS and its own weight rows, and a step is a
 // chain: barrier, first fragments from LDS, MFMAs that each wait for the scales of the one before.  For a tile of
@@ -14,11 +14,11 @@
 //    the requests of one 4-byte copy per row and step (those were 30 % of all L2 requests);
 //  * LDS row r holds 16-byte chunk c at place c ^ (r & 7) ^ (r >> 3 & 1): with c ^ (r & 7) alone, half of the LDS
 //    cycles of the fp8 fragment reads were bank conflicts.
-// The sums see the same terms in the same order as in gemm_tile (rotated starts apart: whole blocks of four steps).  Measured on the 32-expert share of the
-// DeepSeek-shaped layer: 16384 tokens, gate/up 612 -> 498 us, down 346 -> 317; 4096 tokens, 224 -> 218 and 133 -> 121.
+// The sums see the same terms in the same order as in gemm_tile (rotated starts apart: whole blocks of four steps).
+// Measured on the 32-expert share of the DeepSeek-shaped layer: 16384 tokens, gate/up 612 -> 498 us, down 346 -> 317;
+// 4096 tokens, 228 -> 222 and 133 -> 123.
 // Fetching the lines of three steps ahead into L2 as well was slower (498 -> 553): the requests cost more than the
-// latency they hide.  Needs K in whole blocks of four steps (the 16-byte scale copies); other tiles and the half-width
-// items of bf16 launches go through gemm_tile.
+// latency they hide.  Other tiles and half-width items go through gemm_tile.
 #pragma once
 #include <type_traits>
 

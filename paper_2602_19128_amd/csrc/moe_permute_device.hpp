@@ -1,8 +1,8 @@
 // Device code of the sort-scatter (paper Sec. 4.5: tokens reordered by expert into contiguous memory).
 //
 // A stable counting sort of the P (token, slot) pairs by expert id.  The pairs are cut into
-// slices of PM_SLICE, one workgroup of 16 wavefronts each, and the workgroups never talk to each
-// other: every workgroup counts ALL pairs in LDS (how many of each expert lie before its slice,
+// slices of PM_SLICE, one workgroup of 16 wavefronts each (a handful of pairs is one slice of a
+// workgroup of four), and the workgroups never talk to each other: every workgroup counts ALL pairs in LDS (how many of each expert lie before its slice,
 // inside it per wavefront, and after it), which gives it the expert offsets and the first row
 // of each of its wavefronts; then each wavefront walks its contiguous part of the slice in
 // order and ranks equal experts inside a 64-pair batch with ballots.  Counting everything in
@@ -60,7 +60,7 @@ __device__ __forceinline__ void permute_block(const int32_t *__restrict__ ids, i
                                               int block, int nblocks)
 {
     constexpr int WAVES = THREADS / kWave;
-        int *wcount = lds;                         // [WAVES][E]  per-wavefront counts -> write cursors
+    int *wcount = lds;                         // [WAVES][E]  per-wavefront counts -> write cursors
     int *scan_a = wcount + WAVES * E;       // [E]
     int *scan_b = scan_a + E;                  // [E]
     int *first_row = scan_b + E;               // [E+1] exclusive offsets

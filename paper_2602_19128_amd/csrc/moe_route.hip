@@ -113,7 +113,7 @@ __global__ __launch_bounds__(NWV * 64) void router_logits_mfma_kernel(const void
     const int nsteps = (kend - kbeg) / RM_BK;              // H and the split size are multiples of 32
 
     // Token rows go through LDS (every wavefront needs all of them): piece v of this thread is row
-    // (tid + v*512) / 4, 16-byte chunk (tid + v*512) % 4.  The weights of a wavefront's 32 experts
+    // (tid + v*RM_THREADS) / 4, 16-byte chunk (tid + v*RM_THREADS) % 4.  The weights of a wavefront's 32 experts
     // are needed by that wavefront alone, so they are loaded straight into the MFMA layout: lane
     // (l16, lq) holds 8 consecutive k of expert l16 of each block.  Both are requested AHEAD steps
     // before use (register sets in rotation).
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NWV * 64) void router_logits_mfma_kernel(const void
 
     // Epilogue through LDS, so that the partial logits leave as whole rows: lane (l16, lq) holds, per
     // expert block, experts 4*lq..4*lq+3 of token l16 of each token block; a row of the staged tile
-    // is one token's 256 logits (+16 bytes, which spreads the 16 tokens of a write over all banks).
+    // is one token's RM_BE logits (+16 bytes, which spreads the 16 tokens of a write over all banks).
     // The last K step ended with a barrier, so the token stages are free to be overwritten.
     constexpr int OUT_PITCH = RM_BE * 4 + 16;
     static_assert(2 * X_BYTES <= rm_lds_bytes<TB, NWV>(), "token stages");
