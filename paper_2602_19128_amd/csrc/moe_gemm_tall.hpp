@@ -12,8 +12,9 @@
 //    step after next take.  They are issued one by one between MFMAs: in one go they would hold the wavefront up;
 //  * token scales come four K steps at a time, 16 bytes per row, a quarter of the rows with each step: a quarter of
 //    the requests of one 4-byte copy per row and step (those were 30 % of all L2 requests);
-//  * LDS row r holds 16-byte chunk c at place c ^ (r & 7) ^ (r >> 3 & 1): with c ^ (r & 7) alone, half of the LDS
-//    cycles of the fp8 fragment reads were bank conflicts.
+//  * LDS row r holds 16-byte chunk c at place c ^ (r & 7) ^ (r >> 3 & 1): with c ^ (r & 7) alone the sixteen lanes that a
+//    16-byte read serves at a time meet in pairs (bank conflicts of 6.6e7 LDS cycles in 1.5e8 of the launch below; with
+//    the loop as a whole 1.2e7 in 0.7e8).
 // The sums see the same terms in the same order as in gemm_tile (rotated starts apart: whole blocks of four steps).
 // Measured on the 32-expert share of the DeepSeek-shaped layer: 16384 tokens, gate/up 612 -> 498 us, down 346 -> 317;
 // 4096 tokens, 228 -> 222 and 133 -> 123.
@@ -351,9 +352,10 @@ __device__ __forceinline__ void gemm_tile_tall8(const GemmArgs &g, const Item &i
 // requested PF groups of two MFMAs ahead; the barrier of a step sits before its last groups.  Weights have three
 // stages of LDS (their lines come from HBM), token rows two.
 // 4096 Mixtral tokens: gate/up 1708 -> 1658 us, down 866 -> 833 (a library GEMM of the same shape: 1615 for the
-// gate/up part).  The clock is down to 1.65 to 1.8 GHz there: what is left is power more than cycles.
-// For experts of one or two tiles, whose weight stream is the time, gemm_tile is the faster one (4096 DeepSeek tokens,
-// gate/up 2736 us against 2793 with this for all tall tiles): there a wavefront refills its own weights without a barrier.
+// gate/up part).  The clock is down to 1.62 to 1.67 GHz there: what is left is power more than cycles.
+// Experts of one or two tiles stay with gemm_tile, in which a wavefront refills its own weights without a barrier: where
+// the weight stream is the time it is the faster one (4096 DeepSeek tokens, gate/up 2736 us against 2793 with this loop
+// for all tall tiles).  Few experts of two tiles would gain here (eight of 4096 x 14336 with 300 rows each, 622 -> 567).
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // LDS of a tall bf16 tile: two stages of token rows, three of weights.
@@ -648,7 +650,7 @@ __device__ __forceinline__ void gemm_tile_tall16(const GemmArgs &g, const Item &
     const int ct = SH::SPLITK ? item.ct >> 1 : item.ct, kh = SH::SPLITK ? item.ct & 1 : 0;
     const int nk = (int)(row_bytes / GM_STEP_BYTES) / (SH::SPLITK ? 2 : 1);
     // Workgroups that share weight and token lines through L2 start at the same column, experts (XCDs) at different ones:
-    // with a start per workgroup the Mixtral gate/up launch fetched 8.0 GB, with this 3.9.
+    // with a start per workgroup the Mixtral gate/up launch of 4096 tokens fetched 7.9 GB, with this 4.9.
     const int koff = (int)((long)(item.tile.expert * 5 % g.k_groups) * nk / g.k_groups);
     const int wave = __builtin_amdgcn_readfirstlane(tid_opaque >> 6);
     const Tall16Args t{g, item.tile, smem, tid_opaque, tid_opaque & 63, wave, ct, kh, nk, koff,
