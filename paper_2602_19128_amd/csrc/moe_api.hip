@@ -72,7 +72,6 @@ Layout layout_for(const moe_config &c)
     Layout l;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t at = off; off += align_up(bytes ? bytes : 1, 256); return at; };
-    l.route = take(route_workspace_bytes(router_view(c)));
     l.ids = take(P * sizeof(int32_t));
     l.w = take(P * sizeof(float));
     l.offsets = take(((size_t)local_experts(c) + 1) * sizeof(int32_t));
@@ -80,12 +79,16 @@ Layout layout_for(const moe_config &c)
     l.inv = take(P * sizeof(int32_t));
     l.tiles = take((size_t)max_tiles_for(c) * sizeof(moe_tile));
     l.sched = take(MOE_SCHED_INTS * sizeof(int32_t));
+    // The router's partial logits are done with before the expert GEMMs: the slices that an fp8 call of few tokens has
+    // beyond whole scale blocks lie over what those write, so that layers near a limit are not pushed over it.
+    l.route = take(route_workspace_bytes(router_view(c), true));
     l.act = take(P * c.I * act_elem);
     l.act_scale = take(c.dtype == MOE_DTYPE_FP8_E4M3 ? P * (c.I / kQBlock) * sizeof(float) : 0);
     l.y = take(P * c.H * (down_k_split(c, tile_rows_for(c)) > 1 ? 2 * sizeof(float) : 2));   // bf16 rows, or two fp32 partial sums
     l.xq = take(c.quantize_x ? (size_t)c.T * c.H : 0);
     l.xq_scale = take(c.quantize_x ? (size_t)c.T * (c.H / kQBlock) * sizeof(float) : 0);
-    l.total = off;
+    const size_t route_end = align_up(l.route + route_workspace_bytes(router_view(c)), 256);
+    l.total = off > route_end ? off : route_end;
     return l;
 }
 

@@ -79,7 +79,8 @@ inline int set_dynamic_lds(DeviceOnce &once, const void *kern, int bytes)
 }
 
 // ---- per-step launchers (arguments already validated by the C ABI layer) -----
-size_t route_workspace_bytes(const moe_config &c);
+// own: the part that moe_forward's workspace sets aside; the rest lies over sections that are written after routing.
+size_t route_workspace_bytes(const moe_config &c, bool own = false);
 int launch_route(const moe_config &c, const void *x, const float *x_scale, const float *router_w,
                  const float *bias, int32_t *ids, float *w, void *ws, hipStream_t s);
 int launch_quantize_act(const moe_config &c, const void *x, void *xq, float *x_scale, hipStream_t s);

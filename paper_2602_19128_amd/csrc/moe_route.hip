@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256) void router_few_experts_kernel(const void *__r
 //                 64 DeepSeek tokens 17 -> 8 us, 200 tokens 21 -> 10, 333 tokens of 60 experts 6.9 -> 5.0; logits
 //                 as close to float64 as before.  The line: 1024 fp8 tokens 27 us with tall workgroups, 35 with these,
 //                 1500 bf16 tokens 27 and 47
-struct MfmaGrid { bool use, few; int tiles_t, tiles_e, splits, k_per_split; };
+struct MfmaGrid { bool use, few; int tiles_t, tiles_e, splits, k_per_split, block_splits; };   // block_splits: with slices of whole scale blocks
 
 MfmaGrid mfma_grid(const moe_config &c)
 {
@@ -379,12 +379,15 @@ MfmaGrid mfma_grid(const moe_config &c)
         // 64, H = 1024, 7.8 / 6.6; 300 of 256, H = 512, 10.2 / 9.6.  Beyond, the top-k kernel pays for them: 200 of 256,
         // H = 1024, 10.5 and with slices of 32 12.0; 64 of 512, H = 512, 10.8 and 12.9; 511 of 512, H = 256, 11.4 and 12.2.
         auto partials = [&](int p) { return (size_t)ceil_div(c.H, p) * c.T * c.E; };
-        const int whole = ceil_div(per, kQBlock) * kQBlock, eighth = max(per, ceil_div(chunks, 8) * RM_BK);
+        const int whole = ceil_div(per, kQBlock) * kQBlock;
+        g.block_splits = ceil_div(c.H, whole);
+        const int eighth = max(per, ceil_div(chunks, 8) * RM_BK);
         if (!g.few || c.E > 256 || partials(per) >= RM_FEW_PARTIALS)
             per = g.few && eighth < whole && partials(eighth) <= 2 * RM_FEW_PARTIALS ? eighth : whole;
     }
     g.k_per_split = per;
     g.splits = ceil_div(c.H, per);
+    if (c.dtype != MOE_DTYPE_FP8_E4M3) g.block_splits = g.splits;
     return g;
 }
 
@@ -401,12 +404,12 @@ int launch_logits_mfma(const MfmaGrid &m, const moe_config &c, const void *x, co
     return check_launch();
 }
 
-size_t route_workspace_bytes(const moe_config &c)
+size_t route_workspace_bytes(const moe_config &c, bool own)
 {
     if (c.E <= RT_FEW) return 256;
     const MfmaGrid m = mfma_grid(c);
     if (m.use)
-        return align_up((size_t)m.splits * c.T * c.E * sizeof(float), 256);
+        return align_up((size_t)(own ? m.block_splits : m.splits) * c.T * c.E * sizeof(float), 256);
     const RouteGrid g = route_grid(c);
     return align_up((size_t)g.splits * c.T * c.E * sizeof(float), 256);
 }

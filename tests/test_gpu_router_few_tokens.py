@@ -39,3 +39,24 @@ def test_route_few_tokens(wl):
     torch.cuda.synchronize()
     compare_routing(ids_g, w_g, ids, w, margin, wl.routed_scale, wl.E, keys)
     np.testing.assert_allclose(w_g.sum(dim=1).cpu().numpy(), wl.routed_scale, rtol=1e-5)
+
+
+@pytest.mark.parametrize("T, H, I, E", [(201, 512, 128, 256), (1, 128, 128, 256), (300, 256, 256, 64)])
+def test_forward_with_partial_logits_over_later_sections(T, H, I, E):
+    """moe_forward on a workspace of exactly the stated size against its steps, which have scratch of their own."""
+    wl = syn.Workload("overlaid", T=T, H=H, I=I, E=E, top_k=4, fp8=True)
+    gpu = syn.make_inputs(wl, seed=5).to("cuda:0")
+    cfg = moe.MoEConfig.from_workload(wl)
+    ids, w = moe.moe_route(cfg, gpu.x, gpu.x_scale, gpu.router_w, gpu.bias)
+    _, pair, inv, tiles, sched = moe.moe_permute(cfg, ids)
+    act, act_scale = moe.moe_grouped_gemm_swiglu(cfg, gpu.x, gpu.x_scale, gpu.w1, gpu.w1_scale, pair, tiles, sched)
+    ref = moe.moe_combine(cfg, moe.moe_grouped_gemm_down(cfg, act, act_scale, gpu.w2, gpu.w2_scale, tiles, sched), w, inv)
+    size = moe.moe_workspace_size(cfg)
+    for fill in (0, 0xff):
+        ws = torch.full((size + 4096,), fill, dtype=torch.uint8, device="cuda:0")
+        ws[size:] = 0xa5
+        out = moe.moe_forward(cfg, gpu.x, gpu.x_scale, gpu.router_w, gpu.bias, gpu.w1, gpu.w1_scale, gpu.w2, gpu.w2_scale,
+                              workspace=ws[:size])
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+        assert bool((ws[size:] == 0xa5).all())

@@ -133,6 +133,16 @@ def test_static_scratch_entry_refuses_large_problems_without_touching_the_device
     assert int(re.search(r"MOE_STATIC_SCRATCH_BYTES = (\d+) << 20", text).group(1)) << 20 == moe.STATIC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("T, H, I, E", [(415, 2048, 15360, 32), (436, 1024, 16384, 32), (502, 256, 15360, 256)])
+def test_extra_router_slices_do_not_grow_a_forward(lib, T, H, I, E):
+    """fp8 layers of few tokens whose intermediates fill the static scratch almost: the partial logits of the slices
+    beyond whole scale blocks lie over sections that are written after routing."""
+    cfg = moe.MoEConfig(T, H, I, E, 8, 0, 1, 1, 1, 1, 1, 1.0, 0, 0, 0)
+    blocks = -(-H // 128)
+    assert moe.moe_route_workspace_size(cfg) > blocks * T * E * 4 or blocks > 8
+    assert moe.STATIC_SCRATCH_BYTES - (2 << 20) < moe.moe_workspace_size(cfg) <= moe.STATIC_SCRATCH_BYTES
+
+
 def test_parity_cases_reach_the_kernel_shapes_the_benchmarks_run(lib):
     """The launch shape of both grouped GEMMs for every benchmark workload, and the small parity
     cases that are there to reach the same kernel instantiations whole-tile (tests/test_gpu_parity.py)."""
