@@ -10,6 +10,9 @@
 //                         launch may take, which runs this code too.
 //   router_topk_kernel    one 64-lane wavefront per token: scoring rule, optional
 //                         group limiting, then k rounds of a cross-lane arg-max.
+#include <type_traits>
+
+#include "moe_lds_copy.hpp"
 #include "moe_route_device.hpp"
 
 namespace moe {
@@ -36,7 +39,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const void *__restri
 // loaded (a dozen VALU operations per pair of weights, hidden behind the MFMAs): the weights are
 // read as fp32, 4 bytes per element instead of the 6 of stored planes, and no separate pass runs.
 //
-// A workgroup of NWV wavefronts owns TB*16 tokens x NWV*32 experts x one slice of H.  Wavefront w owns
+// Below 512 tokens: a workgroup of NWV wavefronts owns TB*16 tokens x NWV*32 experts x one slice of H.  Wavefront w owns
 // expert blocks 2w, 2w+1 (16 experts each) against all token blocks; per 32-wide K step the
 // workgroup stages the token rows in LDS (double buffered) while every wavefront loads the weights
 // of its own experts straight into registers, both several steps ahead.  fp8 inputs: the payload
@@ -44,6 +47,7 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const void *__restri
 // The partial logits leave through LDS as whole rows.
 typedef __attribute__((ext_vector_type(8))) __bf16 rt_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float rt_f32x4;
+typedef __attribute__((ext_vector_type(16))) float rt_f32x16;
 
 constexpr int RM_MANY_TOKENS = 512;        // from here on the tall workgroups, see mfma_grid
 constexpr size_t RM_FEW_PARTIALS = 512 << 10;   // partial logits (2 MB) that cost less than the round trips they save, see mfma_grid
@@ -69,18 +73,43 @@ __device__ inline uint4 fp8x8_to_bf16x8(uint2 raw)
     return o;
 }
 
-// Two fp32 router weights -> their three bf16 planes (hi, mid, lo: each the bf16 rounding, to nearest
-// even, of what the previous ones leave; the remainders are exact in fp32).
-__device__ inline void split_pair(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo)
+// Two fp32 router weights -> their three bf16 planes (hi, mid, lo: each the bf16 rounding, to nearest even, of what the
+// previous ones leave; the remainders are exact in fp32), one plane at a time: a and b become the remainders.
+__device__ __forceinline__ uint32_t split_piece(float &a, float &b)
 {
-    const rt_bf16x2 h = __builtin_convertvector(rt_f32x2{a, b}, rt_bf16x2);
-    hi = __builtin_bit_cast(uint32_t, h);
-    const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
-    const rt_bf16x2 m = __builtin_convertvector(rt_f32x2{ra, rb}, rt_bf16x2);
-    mid = __builtin_bit_cast(uint32_t, m);
-    const float sa = ra - __uint_as_float(mid << 16), sb = rb - __uint_as_float(mid & 0xffff0000u);
-    const rt_bf16x2 l = __builtin_convertvector(rt_f32x2{sa, sb}, rt_bf16x2);
-    lo = __builtin_bit_cast(uint32_t, l);
+    const uint32_t p = __builtin_bit_cast(uint32_t, __builtin_convertvector(rt_f32x2{a, b}, rt_bf16x2));
+    a -= __uint_as_float(p << 16);
+    b -= __uint_as_float(p & 0xffff0000u);
+    return p;
+}
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo)
+{
+    hi = split_piece(a, b);
+    mid = split_piece(a, b);
+    lo = split_piece(a, b);
+}
+
+// Writes a workgroup's staged logits (BT tokens x BE experts, rows of BE floats and 16 bytes) as whole rows.
+template <int BT, int BE, int THREADS>
+__device__ __forceinline__ void store_logits(const unsigned char *staged, float *__restrict__ dst, int t0, int e0, int T, int E)
+{
+    constexpr int LPR = BE / 4;                            // lanes per row of the tile
+    const int tid = threadIdx.x;
+    const int e = e0 + (tid % LPR) * 4;
+    const bool vec = (E & 3) == 0 && e + 3 < E;
+    for (int r = tid / LPR; r < BT; r += THREADS / LPR) {
+        const int t = t0 + r;
+        if (t >= T) break;
+        const rt_f32x4 v = *reinterpret_cast<const rt_f32x4 *>(staged + r * (BE * 4 + 16) + (tid % LPR) * 16);
+        float *row = dst + (size_t)t * E + e;
+        if (vec) {
+            *reinterpret_cast<rt_f32x4 *>(row) = v;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (e + j < E) row[j] = v[j];
+        }
+    }
 }
 
 // LDS of a workgroup: the staged output tile (the two token stages fit inside).
@@ -252,23 +281,262 @@ __global__ __launch_bounds__(NWV * 64) void router_logits_mfma_kernel(const void
         for (int b = 0; b < 2; ++b)
             *reinterpret_cast<rt_f32x4 *>(rsm + (m * 16 + l16) * OUT_PITCH + ((wave * 2 + b) * 16 + lq * 4) * 4) = acc[b][m];
     __syncthreads();
-    float *dst = zpart + (size_t)zs * T * E;
-    constexpr int LPR = RM_BE / 4;                         // lanes per row of the tile
-    const int e = e0 + (tid % LPR) * 4;
-    const bool vec = (E & 3) == 0 && e + 3 < E;
-    for (int r = tid / LPR; r < BT; r += RM_THREADS / LPR) {
-        const int t = t0 + r;
-        if (t >= T) break;
-        const rt_f32x4 v = *reinterpret_cast<const rt_f32x4 *>(rsm + r * OUT_PITCH + (tid % LPR) * 16);
-        float *row = dst + (size_t)t * E + e;
-        if (vec) {
-            *reinterpret_cast<rt_f32x4 *>(row) = v;
-        } else {
+    store_logits<BT, RM_BE, RM_THREADS>(rsm, zpart + (size_t)zs * T * E, t0, e0, T, E);
+}
+
+// ---- many tokens ----------------------------------------------------------------------------------
+//
+// The same sums by eight wavefronts on 128 tokens x 256 experts, on 32x32x16 MFMAs.  At this size the loop above (with
+// eight wavefronts) waits for the address side of the vector memory path: a fragment load of weights touches 16 or 32 lines
+// of 128 bytes, a part of each at a time, and a compute unit looks up about one line a cycle.  So the weights come as
+// direct copies of whole lines into a ring of LDS that is private to their wavefront (no barrier on
+// their way), are read from there half a step ahead and split while the MFMAs of the half step before run: an MFMA,
+// a piece of the split and a fragment read in turn.  Token rows come the same way; fp8 ones a scale block at a
+// time, and are turned to bf16 in LDS two steps ahead.  The copies run three steps ahead (fp8 token rows up to two
+// blocks), one barrier a step publishes the token rows.  Wavefronts past the last expert only move token rows.
+// 7168-wide layer of 256 experts, register-fed loop / this: 16384 fp8 tokens 209 / 165 us, 4096 fp8 58 / 48.5, 4096 bf16
+// 52 / 47.5, 2500 fp8 46 / 40; 1500 tokens of 64 experts, 2048 wide, 17.9 / 16.4; 1024 fp8 23.5 / 22.0; 1500 bf16 the same.  What is left: the
+// three planes are 180 GFLOP at 16384 tokens, 115 to 140 us at the rate of a large bf16 product on this card; without the
+// copies 15 us less, without the split's arithmetic 25.  (Starting the workgroups of a slice at different columns of it
+// gained nothing; remainders by v_dot2_f32_bf16 instead of shift, mask and subtraction were slower.)
+constexpr int RL_WAVES = 8, RL_THREADS = RL_WAVES * 64;
+constexpr int RL_BT = 128, RL_BE = RL_WAVES * 32;          // tokens and experts of a workgroup
+constexpr int RL_TB = RL_BT / 32;                          // blocks of 32 tokens
+constexpr int RL_W_STAGES = 3, RL_W_STAGE = 32 * 128;      // of one wavefront: 32 experts x 32 k
+constexpr int RL_X_STAGE = RL_BT * 64;                     // 128 tokens x 32 k, bf16
+constexpr int RL_RAW_STAGE = RL_BT * 128;                  // fp8: 128 tokens x 128 k
+constexpr int RL_OUT_PITCH = RL_BE * 4 + 16;               // a token's logits of the staged output tile
+constexpr int RL_W_RING = 0, RL_X_RING = RL_W_RING + RL_WAVES * RL_W_STAGES * RL_W_STAGE;
+
+template <bool FP8> struct LogitsTall {
+    static constexpr int X_STAGES = FP8 ? 3 : 4;
+    static constexpr int RAW_RING = RL_X_RING + X_STAGES * RL_X_STAGE;
+    static constexpr int SC_RING = RAW_RING + (FP8 ? 2 * RL_RAW_STAGE : 0);
+    static constexpr int RINGS = SC_RING + (FP8 ? 3 * RL_BT * 4 : 0);
+    static constexpr int LDS_BYTES = RINGS > RL_BT * RL_OUT_PITCH ? RINGS : RL_BT * RL_OUT_PITCH;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS of one compute unit");
+};
+
+template <bool FP8>
+__global__ __launch_bounds__(RL_THREADS) void router_logits_tall_kernel(const void *__restrict__ x,
+                                                                        const float *__restrict__ x_scale,
+                                                                        const float *__restrict__ router_w,
+                                                                        float *__restrict__ zpart, int T, int H, int E,
+                                                                        int k_per_split, int splits)
+{
+    using L = LogitsTall<FP8>;
+    constexpr int TB = RL_TB, NM = 3 * TB;                 // MFMAs of a half step
+    extern __shared__ __align__(16) unsigned char rsm[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, lh = lane >> 5;
+    // (the slice of H is the fastest index: see router_logits_mfma_kernel)
+    const int zs = blockIdx.x % splits, xt = blockIdx.x / splits;
+    const int t0 = xt * RL_BT, e0 = blockIdx.y * RL_BE;
+    const int kbeg = zs * k_per_split;
+    const int nsteps = (min(H, kbeg + k_per_split) - kbeg) / RM_BK;   // (fp8: slices are whole scale blocks)
+    // first column of step s (past the last step: of the last; its copies are made all the same, so that every step has as many)
+    auto k_of = [&](int s_) __attribute__((always_inline)) { return kbeg + min(s_, nsteps - 1) * RM_BK; };
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr_of(rsm));
+
+    // Weights: copy q of a stage moves rows 8q .. 8q+7 of the wavefront's 32 experts; row r holds 16-byte chunk c at
+    // place c ^ (r & 7) ^ (r >> 3 & 1), which keeps the fragment reads free of bank conflicts.
+    const float *w_ptr[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (e + j < E) row[j] = v[j];
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int r = 8 * q + (lane >> 3);
+        const int c = (lane & 7) ^ (r & 7) ^ (r >> 3 & 1);
+        w_ptr[q] = router_w + (size_t)min(e0 + wave * 32 + r, E - 1) * H + c * 4;   // experts past the end: never stored
     }
+    const uint32_t w_lds = lds0 + RL_W_RING + wave * (RL_W_STAGES * RL_W_STAGE);
+    auto copy_w = [&](int s_, int stage) __attribute__((always_inline)) {
+        const int k0 = k_of(s_);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) copy16_to_lds<false>(w_ptr[q] + k0, w_lds + stage * RL_W_STAGE + q * 1024);
+    };
+    // Token rows (past the last token they repeat it; never stored).  bf16: a wavefront moves 16 rows of a stage; row r holds chunk c at
+    // place c ^ (r >> 2 & 3).  fp8: 16 rows of a scale block in two copies, and scales of 64 rows (waves 0 and 1 alone
+    // would do; all copy them, so that every wavefront has as many copies in flight).
+    const unsigned char *x_ptr[FP8 ? 2 : 1];
+    const float *sc_ptr = nullptr;
+    if constexpr (FP8) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = wave * 16 + q * 8 + (lane >> 3);
+            x_ptr[q] = static_cast<const unsigned char *>(x) + (size_t)min(t0 + r, T - 1) * H + (((lane & 7) ^ (r & 7)) << 4);
+        }
+        sc_ptr = x_scale + (size_t)min(t0 + (wave & 1) * 64 + lane, T - 1) * (H / kQBlock);
+    } else {
+        const int r = wave * 16 + (lane >> 2);
+        x_ptr[0] = static_cast<const unsigned char *>(x) + (size_t)min(t0 + r, T - 1) * H * 2 + (((lane & 3) ^ (r >> 2 & 3)) << 4);
+    }
+    auto copy_x = [&](int s_, int stage) __attribute__((always_inline)) {          // bf16, one step
+        copy16_to_lds<false>(x_ptr[0] + (size_t)k_of(s_) * 2, lds0 + RL_X_RING + stage * RL_X_STAGE + wave * 1024);
+    };
+    auto copy_raw = [&](int s_, int raw, int sc) __attribute__((always_inline)) {  // fp8, the scale block of step s_
+        const int k0 = k_of(s_) & ~(kQBlock - 1);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            copy16_to_lds<false>(x_ptr[FP8 ? q : 0] + k0, lds0 + L::RAW_RING + raw * RL_RAW_STAGE + wave * 2048 + q * 1024);
+        copy4_to_lds(sc_ptr + k0 / kQBlock, lds0 + L::SC_RING + sc * (RL_BT * 4) + (wave & 1) * 256);
+    };
+    // fp8: 8 payload bytes of a step a thread, to the place that the bf16 copies give them
+    const int crow = tid >> 2, cpiece = tid & 3;
+    unsigned char *const conv_dst = rsm + RL_X_RING + crow * 64 + ((cpiece ^ (crow >> 2 & 3)) << 4);
+    auto read_raw = [&](int s_, int raw) __attribute__((always_inline)) {
+        const int c = (s_ & 3) * 2 + (cpiece >> 1);
+        return *reinterpret_cast<const uint2 *>(rsm + L::RAW_RING + raw * RL_RAW_STAGE + crow * 128 + ((c ^ (crow & 7)) << 4) + (cpiece & 1) * 8);
+    };
+
+    // Fragment reads: lane (l32, lh) holds k 16 kk + 8 lh .. +7 of its expert's or token's row.
+    const int wfrag = wave * (RL_W_STAGES * RL_W_STAGE) + RL_W_RING + l32 * 128 + (((2 * lh) ^ (l32 & 7) ^ (l32 >> 3 & 1)) << 4);
+    const int xfrag = RL_X_RING + l32 * 64 + ((lh ^ (l32 >> 2 & 3)) << 4);
+    auto read_w = [&](int stage, int kk, float (&f)[8]) __attribute__((always_inline)) {
+        const int at = (wfrag ^ (kk << 6)) + stage * RL_W_STAGE;
+        const rt_f32x4 a = *reinterpret_cast<const rt_f32x4 *>(rsm + at), b = *reinterpret_cast<const rt_f32x4 *>(rsm + (at ^ 16));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { f[v] = a[v]; f[4 + v] = b[v]; }
+    };
+    auto read_x = [&](int stage, int kk, int m) __attribute__((always_inline)) {
+        return *reinterpret_cast<const rt_bf16x8 *>(rsm + (xfrag ^ (kk << 5)) + stage * RL_X_STAGE + m * 2048);
+    };
+
+    // part, fp8: sum of the current scale block; bf16: sum of the two smaller planes, which apart from the large one
+    // loses less to rounding (error of the routing weights of 4096 tokens 8.0e-8 -> 7.3e-8; the loop takes 1 % longer)
+    rt_f32x16 acc[TB], part[TB];
+#pragma unroll
+    for (int m = 0; m < TB; ++m)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[m][v] = part[m][v] = 0.f;
+
+    uint32_t pl[2][3][4];                                  // [half of the step][plane: hi, mid, lo][pair of k]
+    rt_bf16x8 tf[2][TB];
+    float wr[2][8];                                        // [half of the step] weights to be split
+    // The MFMAs of half kk of a step, smallest plane first (the small contributions meet before the large one is added).
+    // In between: the split of the next half's weights, the reads of its token fragments (of x_stage) and of
+    // the weights of the half after it (of w_stage), which take the place of those split in this one.
+    // FIRST: of an fp8 scale block, whose sums start at zero.
+    auto half_step = [&](auto kk_, auto first_, int x_stage, int w_stage) __attribute__((always_inline)) {
+        constexpr int kk = decltype(kk_)::value;
+        constexpr bool FIRST = decltype(first_)::value;
+        rt_f32x16 zero;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero[v] = 0.f;
+        float f[8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) f[v] = wr[kk ^ 1][v];
+        read_w(w_stage, kk, wr[kk]);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int m = i % TB, p = 2 - i / TB;
+            rt_f32x16 &dst = FP8 || p > 0 ? part[m] : acc[m];
+            dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(rt_bf16x8, uint4{pl[kk][p][0], pl[kk][p][1], pl[kk][p][2], pl[kk][p][3]}), tf[kk][m], FIRST && p == 2 ? zero : dst, 0, 0, 0);
+            if (i < TB) tf[kk ^ 1][i] = read_x(x_stage, kk ^ 1, i);
+            pl[kk ^ 1][i / 4][i % 4] = split_piece(f[2 * (i % 4)], f[2 * (i % 4) + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    static_assert(NM == 12, "a piece of the split per MFMA");
+
+    const bool active = e0 + wave * 32 < E;
+    // Before the loop: weights of steps 0 to 2, token rows of steps 0 to 2 (fp8: of the first two blocks).
+    if constexpr (FP8) {
+        copy_raw(0, 0, 0);
+        copy_w(0, 0);
+        copy_raw(4, 1, 1);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) copy_x(j, j);
+        copy_w(0, 0);
+    }
+    copy_w(1, 1);
+    copy_w(2, 2);
+    MOE_WAIT_VMCNT(4);                                     // all but the last
+    asm volatile("s_barrier" ::: "memory");
+    if constexpr (FP8) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) *reinterpret_cast<uint4 *>(conv_dst + j * RL_X_STAGE) = fp8x8_to_bf16x8(read_raw(j, 0));
+        __syncthreads();
+    }
+    read_w(0, 0, wr[0]);
+    read_w(0, 1, wr[1]);
+#pragma unroll
+    for (int m = 0; m < TB; ++m) tf[0][m] = read_x(0, 0, m);
+#pragma unroll
+    for (int j = 0; j < 12; ++j) pl[0][j / 4][j % 4] = split_piece(wr[0][2 * (j % 4)], wr[0][2 * (j % 4) + 1]);
+
+    int ws = 0, xs = 0, sc = 0;                            // stages of step s in the rings of weights, tokens and (its block's) scales
+    auto step = [&](auto j_, int s) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_)::value;             // fp8: the step's number in its scale block
+        const int w1 = ws == 2 ? 0 : ws + 1;
+        const int x1 = xs == L::X_STAGES - 1 ? 0 : xs + 1;
+        uint2 raw{};
+        if constexpr (FP8) {
+            // the block after next takes the place of this one, whose last step was turned to bf16 in the step before
+            if (j == 2) copy_raw(s + 6, s >> 2 & 1, sc == 0 ? 2 : sc - 1);
+            raw = read_raw(s + 2, (s + 2) >> 2 & 1);
+        } else {
+            copy_x(s + 3, xs == 0 ? 3 : xs - 1);           // (read last in step s - 1)
+        }
+        if (active) {
+            half_step(std::integral_constant<int, 0>{}, std::integral_constant<bool, FP8 && j == 0>{}, xs, w1);
+            copy_w(s + 3, ws);                             // (its last fragments have just been split)
+        }
+        if constexpr (FP8) *reinterpret_cast<uint4 *>(conv_dst + (x1 == 2 ? 0 : x1 + 1) * RL_X_STAGE) = fp8x8_to_bf16x8(raw);
+        if (active) half_step(std::integral_constant<int, 1>{}, std::integral_constant<bool, false>{}, x1, w1);
+        if constexpr (FP8) {
+            if constexpr (j == 3) {                        // the scale block ends here
+#pragma unroll
+                for (int m = 0; m < TB; ++m) {
+                    const float v_sc = *reinterpret_cast<const float *>(rsm + L::SC_RING + sc * (RL_BT * 4) + (m * 32 + l32) * 4);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[m][v] = fmaf(part[m][v], v_sc, acc[m][v]);
+                }
+                sc = sc == 2 ? 0 : sc + 1;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        // Everything issued before this step has landed: the weights and token rows of step s + 2 (this step's: four copies
+        // of weights, and one of token rows or, with a new block, three)
+        constexpr int token_copies = !FP8 ? 1 : j == 2 ? 3 : 0;
+        if (active) MOE_WAIT_VMCNT(4 + token_copies);
+        else MOE_WAIT_VMCNT(token_copies);
+        asm volatile("s_barrier" ::: "memory");
+        ws = w1;
+        xs = x1;
+    };
+    if constexpr (FP8) {
+        for (int s = 0; s < nsteps; s += 4) {
+            step(std::integral_constant<int, 0>{}, s);
+            step(std::integral_constant<int, 1>{}, s + 1);
+            step(std::integral_constant<int, 2>{}, s + 2);
+            step(std::integral_constant<int, 3>{}, s + 3);
+        }
+    } else {
+        for (int s = 0; s < nsteps; ++s) step(std::integral_constant<int, 0>{}, s);
+    }
+    MOE_WAIT_VMCNT(0);                                     // (copies past the last step may be under way)
+    __syncthreads();
+
+    if constexpr (!FP8) {
+#pragma unroll
+        for (int m = 0; m < TB; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][v] += part[m][v];
+    }
+    // Epilogue through LDS, so that the partial logits leave as whole rows: lane (l32, lh) holds experts 8 j + 4 lh .. +3
+    // of token l32 of each token block; a row of the staged tile is one token's logits (+16 bytes, which spreads
+    // the tokens of a write over all banks).
+#pragma unroll
+    for (int m = 0; m < TB; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            *reinterpret_cast<rt_f32x4 *>(rsm + (m * 32 + l32) * RL_OUT_PITCH + (wave * 32 + j * 8 + lh * 4) * 4) =
+                rt_f32x4{acc[m][4 * j], acc[m][4 * j + 1], acc[m][4 * j + 2], acc[m][4 * j + 3]};
+    __syncthreads();
+    store_logits<RL_BT, RL_BE, RL_THREADS>(rsm, zpart + (size_t)zs * T * E, t0, e0, T, E);
 }
 
 // What the logits of the matrix-core kernel were made of (x null: logits of the FMA tiles).
@@ -347,8 +615,8 @@ __global__ __launch_bounds__(256) void router_few_experts_kernel(const void *__r
 }  // namespace
 
 // Matrix-core path: workgroup shape and H split.
-//   many tokens   128 tokens x 256 experts by eight wavefronts (256 tokens measured 9 % slower: twice the
-//                 partial logits), one workgroup per compute unit
+//   many tokens   128 tokens x 256 experts by eight wavefronts (256 tokens measured 9 % slower with the loop of few tokens:
+//                 twice the partial logits), one workgroup per compute unit
 //   few tokens    64 tokens x 128 experts by four wavefronts, as many slices of H as the top-k kernel loads
 //                 together: such a call is a chain of memory round trips, and more workgroups with shorter slices
 //                 shorten it.  Against the FMA tiles it replaced, whose stages each waited for their own loads:
@@ -391,16 +659,17 @@ MfmaGrid mfma_grid(const moe_config &c)
     return g;
 }
 
-template <bool FP8, int TB, int NWV>
+template <bool FP8>
 int launch_logits_mfma(const MfmaGrid &m, const moe_config &c, const void *x, const float *x_scale,
                        const float *router_w, float *zpart, hipStream_t s)
 {
-    auto kern = router_logits_mfma_kernel<FP8, TB, NWV>;
-    static DeviceOnce lds_limit_set;
-    const int rc = set_dynamic_lds(lds_limit_set, reinterpret_cast<const void *>(kern), rm_lds_bytes<TB, NWV>());
+    auto kern = m.few ? router_logits_mfma_kernel<FP8, 4, 4> : router_logits_tall_kernel<FP8>;
+    const int threads = m.few ? 256 : RL_THREADS, lds = m.few ? rm_lds_bytes<4, 4>() : LogitsTall<FP8>::LDS_BYTES;
+    static DeviceOnce few_limit_set, tall_limit_set;
+    const int rc = set_dynamic_lds(m.few ? few_limit_set : tall_limit_set, reinterpret_cast<const void *>(kern), lds);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL(kern, dim3(m.tiles_t * m.splits, m.tiles_e, 1), dim3(NWV * 64), (rm_lds_bytes<TB, NWV>()), s, x, x_scale,
-                       router_w, zpart, c.T, c.H, c.E, m.k_per_split, m.splits);
+    hipLaunchKernelGGL(kern, dim3(m.tiles_t * m.splits, m.tiles_e, 1), dim3(threads), lds, s, x, x_scale, router_w, zpart,
+                       c.T, c.H, c.E, m.k_per_split, m.splits);
     return check_launch();
 }
 
@@ -444,10 +713,8 @@ int launch_route(const moe_config &c, const void *x, const float *x_scale, const
     const MfmaGrid m = mfma_grid(c);
     const bool f8 = c.dtype == MOE_DTYPE_FP8_E4M3;
     if (m.use) {
-        const int rc = m.few ? (f8 ? launch_logits_mfma<true, 4, 4>(m, c, x, x_scale, router_w, zpart, s)
-                                   : launch_logits_mfma<false, 4, 4>(m, c, x, x_scale, router_w, zpart, s))
-                             : (f8 ? launch_logits_mfma<true, 8, 8>(m, c, x, x_scale, router_w, zpart, s)
-                                   : launch_logits_mfma<false, 8, 8>(m, c, x, x_scale, router_w, zpart, s));
+        const int rc = f8 ? launch_logits_mfma<true>(m, c, x, x_scale, router_w, zpart, s)
+                          : launch_logits_mfma<false>(m, c, x, x_scale, router_w, zpart, s);
         if (rc != MOE_OK) return rc;
         p.splits = m.splits;
     } else {
