@@ -780,6 +780,14 @@ __global__ __launch_bounds__(SH::THREADS) void grouped_gemm_kernel(GemmArgs g, c
     gemm_items<SH>(g, tiles, sched, col_tiles, order, round_slots, (int)blockIdx.x, (int)gridDim.x, smem);
 }
 
+// Workgroups of a shape that a compute unit runs at once: its LDS (160 KiB) and wavefront slots (32) decide.
+template <class SH>
+constexpr int per_compute_unit()
+{
+    const int by_lds = (160 * 1024) / SH::LDS_BYTES, by_waves = 32 / SH::NW, n = by_lds < by_waves ? by_lds : by_waves;
+    return n < 1 ? 1 : n;
+}
+
 // Grid and item walk of a launch.
 struct LaunchPlan { int col_tiles, round_slots, blocks, order; };
 
@@ -788,10 +796,7 @@ LaunchPlan launch_plan(const GemmArgs &g, int max_tiles, int est_tiles)
 {
     LaunchPlan p;
     p.col_tiles = ceil_div(g.n_out, SH::COLS) * (SH::SPLITK ? 2 : 1);   // split K: two items per column slab
-    // workgroups one XCD runs at once: LDS (160 KiB) and wavefront slots (32) of a compute unit decide it
-    int per_cu = (160 * 1024) / SH::LDS_BYTES;
-    if (per_cu > 32 / SH::NW) per_cu = 32 / SH::NW;
-    p.round_slots = (GM_CUS / GM_XCDS) * (per_cu < 1 ? 1 : per_cu);
+    p.round_slots = (GM_CUS / GM_XCDS) * per_compute_unit<SH>();   // workgroups one XCD runs at once
     // a part holds about an eighth of the tiles; the slack (a tile's slabs, and the half-width items
     // of a last round) keeps the loop in the kernel at one trip, unless hot experts make a range longer than that
     const int part_slots = (ceil_div(max_tiles, GM_XCDS) + 1) * p.col_tiles + (SH::HALF_ITEMS ? p.round_slots / 2 : 0);
@@ -823,9 +828,31 @@ struct ShapesFor {
     // (Four token and five weight stages in flight for launches of fewer workgroups than compute units are slower, at
     // every length of K: down projection of one token, 2048 x 8192, 50 -> 58 us, of three Mixtral tokens 97 -> 102.)
     using Narrow = Shape<MB_MAX, 4, DA, 3, SWIGLU, FP8>;
+    using NarrowShallow = Shape<MB_MAX, 4, 1, 2, SWIGLU, FP8>;    // a stage less in each ring, see narrow_shallow
     using Wide4 = Shape<MB_MAX, 8, DA, DW, SWIGLU, FP8, SWIGLU ? 2 : 4>;
     using WideSplit = Shape<MB_MAX, 8, DA, DW, false, false, 2, true>;
 };
+
+// Whether a narrow launch of `items` takes the shallow rings.  With them a compute unit runs two workgroups with tiles of
+// 128 rows instead of one, three with 64 rows instead of two, four with lower ones instead of two; side by side each is slower by
+// about as much, so what counts is how the items fill the rounds: shallow where its rounds hold no more workgroups than
+// the deep ones do.  Deep / shallow, us (K steps, items), weights rotated through more than the caches:
+//   128 rows  down (11, 480) 24.4 / 21.8, (11, 960) 45.4 / 39.7; gate/up (16, 880) 62.1 / 53.2; left deep (32, 768) 82.4 / 84.2
+//   64 rows   333 tokens of 60 experts of 1344 x 704, down (11, 660) 27.1 / 24.4, gate/up (21, 660) 41.2 / 40.3;
+//             gate/up (12, 720) 33.1 / 27.8, (32, 768) 68 / 66; left deep (11, 960) 31.6 / 33.2, (16, 880) 42.4 / 46.1
+//   lower     gate/up (12, 720) 30.2 / 27.1, (21, 768) 43.0 / 39.1, (16, 880) 40.2 / 40.8; left deep (24, 180) 16.5 / 18.1
+// A long K wants the longer way ahead where two workgroups have it: unless shallow rounds hold fewer workgroups and the
+// last deep one is not a short one.  64 rows (32, 660) 58.1 / 59.9; 16 rows, DeepSeek-shaped, 3 tokens, gate/up (112, 768)
+// 190 / 193, 2 tokens, down (32, 896) 74 / 75.
+template <class DEEP, class SHALLOW>
+bool narrow_shallow(int items, int k_steps)
+{
+    constexpr int d = per_compute_unit<DEEP>(), s = per_compute_unit<SHALLOW>();
+    const int hold_deep = ceil_div(items, d * GM_CUS) * d, hold_shallow = ceil_div(items, s * GM_CUS) * s;
+    if (s <= d || hold_shallow > hold_deep) return false;
+    if (d == 1 || k_steps < 24) return true;
+    return hold_shallow < hold_deep && 8 * (items % (d * GM_CUS)) >= 3 * d * GM_CUS;
+}
 
 template <int MB_MAX, bool SWIGLU, bool FP8>
 int launch_for_rows(const GemmArgs &g, const moe_tile *tiles, const int32_t *sched, int max_tiles, int est_tiles,
@@ -843,8 +870,14 @@ int launch_for_rows(const GemmArgs &g, const moe_tile *tiles, const int32_t *sch
             return launch_shape<typename SF::Wide4>(g, tiles, sched, max_tiles, est_tiles, s);
         return MOE_ERR_UNSUPPORTED;
     case GEMM_NARROW:
-        if constexpr (!(FP8 && SWIGLU))
+        if constexpr (!(FP8 && SWIGLU)) {
+            if constexpr (MB_MAX <= 8) {
+                if (narrow_shallow<typename SF::Narrow, typename SF::NarrowShallow>(
+                        est_tiles * ceil_div(g.n_out, SF::Narrow::COLS), g.K * (FP8 ? 1 : 2) / GM_STEP_BYTES))
+                    return launch_shape<typename SF::NarrowShallow>(g, tiles, sched, max_tiles, est_tiles, s);
+            }
             return launch_shape<typename SF::Narrow>(g, tiles, sched, max_tiles, est_tiles, s);
+        }
         return MOE_ERR_UNSUPPORTED;
     default:
         return launch_shape<typename SF::Wide>(g, tiles, sched, max_tiles, est_tiles, s);
