@@ -10,7 +10,7 @@ constexpr int PM_THREADS = 1024;
 // 5.4 -> 4.4 us).  The ranking of more experts than this wants the threads.
 constexpr int PM_FEW_THREADS = 256, PM_FEW_PAIRS = 256, PM_FEW_EXPERTS = 64;
 
-template <int THREADS>
+template <int THREADS, bool VEC = false>
 __global__ __launch_bounds__(THREADS) void permute_kernel(const int32_t *__restrict__ ids, int P, int E,
                                                              int e_first, int tile_rows, int max_tiles,
                                                              int32_t *__restrict__ offsets,
@@ -20,7 +20,7 @@ __global__ __launch_bounds__(THREADS) void permute_kernel(const int32_t *__restr
                                                              int32_t *__restrict__ sched)
 {
     extern __shared__ int lds[];
-    permute_block<THREADS>(ids, P, E, e_first, tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched, lds,
+    permute_block<THREADS, VEC>(ids, P, E, e_first, tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched, lds,
                               (int)blockIdx.x, (int)gridDim.x);
 }
 
@@ -40,9 +40,9 @@ int launch_permute(const moe_config &c, int tile_rows, int max_tiles, const int3
     }
     const size_t lds = sizeof(int) * permute_lds_ints(PM_THREADS, el);
     const int wgs = min(PM_MAX_WGS, max(1, ceil_div(P, PM_SLICE)));
-    hipLaunchKernelGGL(permute_kernel<PM_THREADS>, dim3(wgs), dim3(PM_THREADS), lds, s, ids, P, el, c.local_expert_offset,
-                       tile_rows, max_tiles,
-                       offsets, sorted_pair, inv, tiles, sched);
+    const bool vec = wgs >= PM_VEC_WGS && ((uintptr_t)ids & 15) == 0;
+    hipLaunchKernelGGL((vec ? permute_kernel<PM_THREADS, true> : permute_kernel<PM_THREADS>), dim3(wgs), dim3(PM_THREADS), lds, s,
+                       ids, P, el, c.local_expert_offset, tile_rows, max_tiles, offsets, sorted_pair, inv, tiles, sched);
     return check_launch();
 }
 

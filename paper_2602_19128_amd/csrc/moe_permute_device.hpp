@@ -25,7 +25,8 @@ namespace {
 
 constexpr int PM_BATCH = 8;             // 64-pair batches whose ids are loaded together
 constexpr int PM_SLICE = 1024;          // pairs placed by one workgroup (one 64-pair batch per wavefront)
-constexpr int PM_MAX_WGS = 64;
+constexpr int PM_MAX_WGS = 128;
+constexpr int PM_VEC_WGS = 16;          // slices from which the ids are counted four at a time
 
 // Inclusive scan of n <= kMaxExperts ints held in LDS (Hillis-Steele, all threads sync).
 __device__ inline void block_inclusive_scan(int *a, int *b, int n, int tid)
@@ -52,7 +53,10 @@ inline __host__ __device__ size_t permute_lds_ints(int threads, int E)
     return (size_t)(threads / kWave) * E + 7 * (size_t)E + 1 + 2 * eq;
 }
 
-template <int THREADS>
+// VEC: many slices, an id list on 16 bytes.  Every workgroup counts every pair, which is then bound by the instruction rate of
+// its compute unit: 131072 pairs 25 -> 15.5 us, 72000 17 -> 12, 32768 over 32 of 256 experts 10.5 -> 8.7.  (Fewer
+// slices are slower that way: 512 pairs 10.7 -> 11.5, 1998 pairs 7.0 -> 7.5.)
+template <int THREADS, bool VEC = false>
 __device__ __forceinline__ void permute_block(const int32_t *__restrict__ ids, int P, int E, int e_first, int tile_rows,
                                               int max_tiles, int32_t *__restrict__ offsets,
                                               int32_t *__restrict__ sorted_pair, int32_t *__restrict__ inv,
@@ -87,7 +91,30 @@ __device__ __forceinline__ void permute_block(const int32_t *__restrict__ ids, i
 
     // pass 1: count every pair once (integer LDS adds: order-independent).  The ids of PM_BATCH
     // strides are requested together so that their latencies overlap.
-    for (int base = 0; base < P; base += PM_BATCH * THREADS) {
+    int counted = 0;                           // (a multiple of 4)
+    if constexpr (VEC) {
+        // Four ids a load, and one look for where they lie: slices and the parts of wavefronts are multiples of 64 pairs.
+        const int nvec = P / 4;
+        for (int base = 0; base < nvec; base += PM_BATCH * THREADS) {
+            int4 ev[PM_BATCH];
+#pragma unroll
+            for (int j = 0; j < PM_BATCH; ++j)
+                ev[j] = reinterpret_cast<const int4 *>(ids)[min(base + j * THREADS + tid, nvec - 1)];
+#pragma unroll
+            for (int j = 0; j < PM_BATCH; ++j) {
+                const int c = base + j * THREADS + tid, p = 4 * c;
+                if (c >= nvec) continue;
+                int *bin = p < s_beg ? before : after;
+                if (p >= s_beg && p < s_end) bin = wcount + ((p - s_beg) / per_wave) * E;
+                const int e[4] = {ev[j].x - e_first, ev[j].y - e_first, ev[j].z - e_first, ev[j].w - e_first};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if ((unsigned)e[i] < (unsigned)E) atomicAdd(&bin[e[i]], 1);
+            }
+        }
+        counted = 4 * nvec;
+    }
+    for (int base = counted; base < P; base += PM_BATCH * THREADS) {
         int ev[PM_BATCH];
 #pragma unroll
         for (int j = 0; j < PM_BATCH; ++j) {

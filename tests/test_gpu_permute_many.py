@@ -1,0 +1,46 @@
+"""Sort-scatter of many slices, whose workgroups count four ids a load: both sides of the line, a number of pairs that is no
+multiple of 4, more slices than workgroups, dropped and out-of-range ids, a local share, ids off the 16-byte grid."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_19128_amd import binding as moe
+from paper_2602_19128_amd import synthetic as syn
+from parity_util import check_tiles, local_permute
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T, k, E, lo, n", [(3840, 4, 64, 0, 0), (15361, 1, 300, 0, 0), (5123, 3, 256, 32, 32),
+                                            (16387, 8, 256, 96, 32), (17500, 8, 40, 0, 0), (131075, 2, 512, 0, 0)])
+def test_permute_many_pairs(T, k, E, lo, n):
+    cfg = moe.MoEConfig.from_workload(syn.Workload("many_pairs", T=T, H=128, I=64, E=E, top_k=k, local_offset=lo, local_experts=n))
+    rng = np.random.default_rng(T + E)
+    ids = rng.integers(0, E, size=(T, k)).astype(np.int32)
+    ids[rng.random((T, k)) < 0.2] = lo                       # one expert above the others
+    off_r, sp_r, inv_r, kept = local_permute(ids, E, lo, n)
+    for shift in (0, 1):
+        ids_g = torch.empty(T * k + shift, dtype=torch.int32, device="cuda")[shift:].view(T, k).copy_(torch.from_numpy(ids))
+        assert ids_g.data_ptr() % 16 == 4 * shift
+        off, sp, inv, tiles, sched = moe.moe_permute(cfg, ids_g)
+        torch.cuda.synchronize()
+        assert np.array_equal(off.cpu().numpy(), off_r)
+        assert np.array_equal(sp.cpu().numpy()[:kept], sp_r)
+        assert np.array_equal(inv.cpu().numpy(), inv_r)
+        check_tiles(tiles, sched, off_r, moe.moe_tile_rows(cfg))
+
+
+def test_dropped_ids_of_many_pairs():
+    T, k, E = 16384, 2, 60
+    cfg = moe.MoEConfig.from_workload(syn.Workload("dropped", T=T, H=128, I=64, E=E, top_k=k))
+    rng = np.random.default_rng(1)
+    ids = rng.integers(-3, E + 3, size=(T, k)).astype(np.int32)
+    ids[0, 0], ids[1, 1] = np.iinfo(np.int32).min, np.iinfo(np.int32).max
+    off, sp, inv, tiles, sched = moe.moe_permute(cfg, torch.from_numpy(ids).cuda())
+    torch.cuda.synchronize()
+    flat, valid = ids.reshape(-1), (ids.reshape(-1) >= 0) & (ids.reshape(-1) < E)
+    order = np.flatnonzero(valid)[np.argsort(flat[valid], kind="stable")]
+    inv_r = np.full(T * k, -1, dtype=np.int32)
+    inv_r[order] = np.arange(order.size)
+    assert np.array_equal(sp.cpu().numpy()[:order.size], order) and np.array_equal(inv.cpu().numpy(), inv_r)
+    assert np.array_equal(np.diff(off.cpu().numpy()), np.bincount(flat[valid], minlength=E))
