@@ -5,7 +5,8 @@
 //   router_logits_mfma_kernel  z = x . router_w^T on the matrix cores, three bf16 MFMAs per block
 //                         carry the fp32 weights exactly; split along H so that a handful of
 //                         decode tokens still fills the chip; partial sums go to scratch and are
-//                         added in a fixed order (deterministic).
+//                         added in a fixed order (deterministic).  From 512 tokens on router_logits_tall_kernel,
+//                         whose weights and token rows come through LDS.
 //   router_logits_kernel  the same partial sums with LDS-tiled fp32 FMAs: the layers that the single
 //                         launch may take, which runs this code too.
 //   router_topk_kernel    one 64-lane wavefront per token: scoring rule, optional
